@@ -2,10 +2,11 @@
 // with GELU (tanh form), trained on labels the exact scan-region criterion
 // produces, used for the particles lambda_min alone cannot decide.
 //
-// Training (FP32, hand-written): forward with stored activations (one wave
-// per row, one lane per hidden unit), weighted binary cross-entropy on the
-// logit, backward pass, parameter gradients as fixed-order batch reductions
-// (deterministic), Adam with bias correction.
+// Training (FP32, hand-written): per batch one kernel for forward, weighted
+// binary cross-entropy on the logit, backward pass and the blocks' parameter
+// gradients (one wave per row, one lane per hidden unit), and one that sums
+// the blocks in a fixed order (deterministic) and applies Adam with bias
+// correction.
 //
 // Inference (BF16 MFMA, FP32 accumulate): one wave handles 16 rows per
 // iteration; layer 1 is a 16x16x32 bf16 MFMA per 16-unit tile with K = 16
@@ -14,6 +15,7 @@
 // the operand layout through LDS), layer 3 a FP32 dot product reduced across
 // the 16 lanes that share a row.  Weights stay in registers for the whole
 // (persistent, grid-stride) kernel.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -50,10 +52,11 @@ __device__ __forceinline__ float gelu_fast(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-__device__ __forceinline__ float gelu_grad_f(float z) {
-  const float c = 0.7978845608028654f;
-  const float th = tanhf(c * (z + 0.044715f * z * z * z));
-  return 0.5f * (1.0f + th) + 0.5f * z * (1.0f - th * th) * c * (1.0f + 3.0f * 0.044715f * z * z);
+// Orders the LDS writes of a wave before its later reads by other lanes.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // ------------------------------------------------------------- training
@@ -97,97 +100,170 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const float *__restrict__ w, co
   if (on && lane == 0) s[b] = p + w[kOffB3];
 }
 
-// dL/ds for the weighted mean BCE and the per-row loss terms.
-__global__ void k_mlp_loss(const float *__restrict__ s, const float *__restrict__ y, const float *__restrict__ wt,
-                           const int32_t *__restrict__ perm, int64_t off, int64_t B, float *__restrict__ ds,
-                           float *__restrict__ lrow) {
-  int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const int64_t row = perm ? (int64_t)perm[off + b] : off + b;
-  const float sv = s[b], yv = y[row], wv = wt ? wt[row] : 1.0f;
-  const float sig = 1.0f / (1.0f + expf(-sv));
-  ds[b] = wv * (sig - yv) / (float)B;
-  lrow[b] = wv * (fmaxf(sv, 0.0f) - sv * yv + log1pf(expf(-fabsf(sv))));
+// tanh form of GELU and its derivative from one tanh.
+__device__ __forceinline__ void gelu_both(float z, float &a, float &d) {
+  const float c = 0.7978845608028654f;
+  const float th = tanhf(c * (z + 0.044715f * z * z * z));
+  a = 0.5f * z * (1.0f + th);
+  d = 0.5f * (1.0f + th) + 0.5f * z * (1.0f - th * th) * c * (1.0f + 3.0f * 0.044715f * z * z);
 }
 
-// Backward through layers 3 and 2 per row: dz2 = ds W3 gelu'(z2); then
-// dz1 = (dz2 W2^T) gelu'(z1).  One wave per row.
-__global__ void __launch_bounds__(256) k_mlp_bwd_rows(const float *__restrict__ w, const float *__restrict__ z1,
-                                                      const float *__restrict__ z2, const float *__restrict__ ds,
-                                                      int64_t B, float *__restrict__ dz1, float *__restrict__ dz2) {
-  __shared__ float sd[4][kMlpHid];
-  const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
-  const int64_t b = (int64_t)blockIdx.x * 4 + r;
-  const bool on = b < B;
-  float d2 = 0.0f;
-  if (on) d2 = ds[b] * w[kOffW3 + lane] * gelu_grad_f(z2[b * kMlpHid + lane]);
-  sd[r][lane] = d2;
-  __syncthreads();
-  if (!on) return;
-  dz2[b * kMlpHid + lane] = d2;
-  float a = 0.0f;
-  for (int k = 0; k < kMlpHid; ++k) a += sd[r][k] * w[kOffW2 + lane * kMlpHid + k];
-  dz1[b * kMlpHid + lane] = a * gelu_grad_f(z1[b * kMlpHid + lane]);
-}
+// Loss and parameter gradients of a batch, summed over the rows of a block:
+// part[block][0 .. kMlpParams) and the block's loss at [kMlpParams].
+//
+// One wave per row, lane = hidden unit, rpw rows per wave.  A lane keeps its
+// column and its row of W2 and its column of W1 in registers (144 values) and
+// the gradients of its columns of W1 and W2 (80 sums), so a row costs 224 FMAs
+// per lane and a few LDS broadcasts, and the activations never reach memory.
+// The four waves' sums are added in wave order, the blocks' in block order by
+// k_mlp_reduce: the result depends only on the rows' order.  It replaces one
+// kernel each for forward, loss and rows' backward pass and one thread per
+// parameter that walked the whole batch: an epoch of 65,536 rows in batches
+// of 4,096 took 31.9 ms, 97% of it in that walk, and takes 0.47 ms (19 us a
+// batch here and 7 us in the reduction).
+constexpr int kPart = kMlpParams + 1;
 
-// Parameter gradients: one thread per parameter, a fixed-order loop over the
-// batch (deterministic).  a1 is recomputed from z1.
-__global__ void __launch_bounds__(256) k_mlp_param_grad(const float *__restrict__ xs, const float *__restrict__ z1,
-                                                        const float *__restrict__ a2, const float *__restrict__ ds,
-                                                        const float *__restrict__ dz1, const float *__restrict__ dz2,
-                                                        int64_t B, float *__restrict__ g) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kMlpParams) return;
-  float acc = 0.0f;
-  if (p < kOffB1) {  // W1[i, o]
-    const int i = p / kMlpHid, o = p % kMlpHid;
-    for (int64_t b = 0; b < B; ++b) acc += xs[b * kMlpIn + i] * dz1[b * kMlpHid + o];
-  } else if (p < kOffW2) {  // b1[o]
-    const int o = p - kOffB1;
-    for (int64_t b = 0; b < B; ++b) acc += dz1[b * kMlpHid + o];
-  } else if (p < kOffB2) {  // W2[k, o]
-    const int q = p - kOffW2, k = q / kMlpHid, o = q % kMlpHid;
-    for (int64_t b = 0; b < B; ++b) acc += gelu_f(z1[b * kMlpHid + k]) * dz2[b * kMlpHid + o];
-  } else if (p < kOffW3) {  // b2[o]
-    const int o = p - kOffB2;
-    for (int64_t b = 0; b < B; ++b) acc += dz2[b * kMlpHid + o];
-  } else if (p < kOffB3) {  // W3[k]
-    const int k = p - kOffW3;
-    for (int64_t b = 0; b < B; ++b) acc += a2[b * kMlpHid + k] * ds[b];
-  } else {  // b3
-    for (int64_t b = 0; b < B; ++b) acc += ds[b];
+__global__ void __launch_bounds__(256, 1) k_mlp_grad(const float *__restrict__ w, const float *__restrict__ mean,
+                                                     const float *__restrict__ std, const float *__restrict__ X,
+                                                     const float *__restrict__ y, const float *__restrict__ wt,
+                                                     const int32_t *__restrict__ perm, int64_t off, int64_t B, int rpw,
+                                                     float *__restrict__ part) {
+  __shared__ __align__(16) float sx[4][kMlpIn], sa[4][kMlpHid], sd[4][kMlpHid];
+  __shared__ float sum[kPart];
+  const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
+  float w1[kMlpIn], w2c[kMlpHid], w2r[kMlpHid];
+#pragma unroll
+  for (int i = 0; i < kMlpIn; ++i) w1[i] = w[kOffW1 + i * kMlpHid + lane];
+#pragma unroll
+  for (int k = 0; k < kMlpHid; ++k) w2c[k] = w[kOffW2 + k * kMlpHid + lane];
+  static_assert(kOffW2 % 4 == 0, "rows of W2 are read four values at a time (the trainer's weights are 256-byte aligned)");
+#pragma unroll
+  for (int k = 0; k < kMlpHid; k += 4) {
+    const float4 q = *reinterpret_cast<const float4 *>(w + kOffW2 + lane * kMlpHid + k);
+    w2r[k] = q.x;
+    w2r[k + 1] = q.y;
+    w2r[k + 2] = q.z;
+    w2r[k + 3] = q.w;
   }
-  g[p] = acc;
-}
-
-// Fixed-order sum of the row losses divided by B.
-__global__ void __launch_bounds__(256) k_mlp_loss_sum(const float *__restrict__ lrow, int64_t B, float *__restrict__ out) {
-  __shared__ float sh[256];
-  float a = 0.0f;
-  for (int64_t b = threadIdx.x; b < B; b += 256) a += lrow[b];
-  sh[threadIdx.x] = a;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
+  const float b1 = w[kOffB1 + lane], b2 = w[kOffB2 + lane], w3 = w[kOffW3 + lane], b3 = w[kOffB3];
+  float g1[kMlpIn], g2[kMlpHid], gb1 = 0.0f, gb2 = 0.0f, g3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kMlpIn; ++i) g1[i] = 0.0f;
+#pragma unroll
+  for (int k = 0; k < kMlpHid; ++k) g2[k] = 0.0f;
+  const int64_t b0 = ((int64_t)blockIdx.x * 4 + v) * rpw;
+  const int64_t b_end = b0 + rpw < B ? b0 + rpw : B;
+  for (int64_t b = b0; b < b_end; ++b) {
+    const int64_t row = perm ? (int64_t)perm[off + b] : off + b;
+    if (lane < kMlpIn) sx[v][lane] = (X[row * kMlpIn + lane] - mean[lane]) / std[lane];
+    wave_lds_order();
+    float z = b1;
+#pragma unroll
+    for (int i = 0; i < kMlpIn; ++i) z += sx[v][i] * w1[i];
+    float a1, d1, a2, d2;
+    gelu_both(z, a1, d1);
+    sa[v][lane] = a1;
+    wave_lds_order();
+    float q = b2;
+#pragma unroll
+    for (int k = 0; k < kMlpHid; ++k) q += sa[v][k] * w2c[k];
+    gelu_both(q, a2, d2);
+    float s = a2 * w3;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    s += b3;
+    // dL/ds of the weighted mean BCE and the row's loss
+    const float yv = y[row], wv = wt ? wt[row] : 1.0f;
+    const float sig = 1.0f / (1.0f + expf(-s));
+    const float ds = wv * (sig - yv) / (float)B;
+    loss += wv * (fmaxf(s, 0.0f) - s * yv + log1pf(expf(-fabsf(s))));
+    // back through layers 3 and 2
+    const float e2 = ds * w3 * d2;
+    sd[v][lane] = e2;
+    wave_lds_order();
+    float t = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kMlpHid; ++k) t += sd[v][k] * w2r[k];
+    const float e1 = t * d1;
+#pragma unroll
+    for (int i = 0; i < kMlpIn; ++i) g1[i] += sx[v][i] * e1;
+#pragma unroll
+    for (int k = 0; k < kMlpHid; ++k) g2[k] += sa[v][k] * e2;
+    gb1 += e1;
+    gb2 += e2;
+    g3 += a2 * ds;
+    gb3 += ds;
+    wave_lds_order();  // the row's LDS is rewritten for the next one
+  }
+  for (int u = 0; u < 4; ++u) {
+    if (v == u) {
+      auto put = [&](int p, float x) { sum[p] = u == 0 ? x : sum[p] + x; };
+#pragma unroll
+      for (int i = 0; i < kMlpIn; ++i) put(kOffW1 + i * kMlpHid + lane, g1[i]);
+      put(kOffB1 + lane, gb1);
+#pragma unroll
+      for (int k = 0; k < kMlpHid; ++k) put(kOffW2 + k * kMlpHid + lane, g2[k]);
+      put(kOffB2 + lane, gb2);
+      put(kOffW3 + lane, g3);
+      if (lane == 0) {
+        put(kOffB3, gb3);
+        put(kMlpParams, loss);
+      }
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = sh[0] / (float)B;
+  for (int p = threadIdx.x; p < kPart; p += 256) part[(size_t)blockIdx.x * kPart + p] = sum[p];
 }
 
-__global__ void k_mlp_loss_acc(const float *loss, float *acc, int reset) {
-  *acc = (reset ? 0.0f : *acc) + *loss;
+// Sums the blocks' partial gradients (and the losses: *loss the batch mean,
+// acc += or = it) and, with adam, updates the parameters.  kRedParams
+// parameters per block, each summed by kRedSlices threads over a contiguous
+// share of the blocks: one thread per parameter waited out a serial chain of
+// loads on 21 of 256 CUs.
+constexpr int kRedParams = 64, kRedSlices = 16;
+
+struct AdamArgs {
+  float *w, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const AdamArgs &A, int p, float gp) {
+  const float mp = A.b1 * A.m[p] + (1.0f - A.b1) * gp;
+  const float vp = A.b2 * A.v[p] + (1.0f - A.b2) * gp * gp;
+  A.m[p] = mp;
+  A.v[p] = vp;
+  A.w[p] -= A.lr * (mp / A.c1) / (sqrtf(vp / A.c2) + A.eps);
 }
 
-__global__ void k_mlp_adam(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
-                           float *__restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
+__global__ void __launch_bounds__(kRedParams *kRedSlices)
+    k_mlp_reduce(const float *__restrict__ part, int nblk, int64_t B, float *__restrict__ g, float *__restrict__ loss,
+                 float *acc, int acc_reset, int adam, AdamArgs A) {
+  __shared__ float sh[kRedSlices][kRedParams];
+  const int c = threadIdx.x & (kRedParams - 1), sl = threadIdx.x / kRedParams;
+  const int p = blockIdx.x * kRedParams + c;
+  const int per = (nblk + kRedSlices - 1) / kRedSlices;
+  const int k0 = sl * per, k1 = k0 + per < nblk ? k0 + per : nblk;
+  float t = 0.0f;
+  if (p < kPart)
+    for (int k = k0; k < k1; ++k) t += part[(size_t)k * kPart + p];
+  sh[sl][c] = t;
+  __syncthreads();
+  if (sl != 0 || p >= kPart) return;
+#pragma unroll
+  for (int k = 1; k < kRedSlices; ++k) t += sh[k][c];
+  if (p == kMlpParams) {
+    t /= (float)B;
+    *loss = t;
+    if (acc) *acc = (acc_reset ? 0.0f : *acc) + t;
+    return;
+  }
+  g[p] = t;
+  if (adam) adam_update(A, p, t);
+}
+
+__global__ void k_mlp_adam(const float *__restrict__ g, AdamArgs A) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kMlpParams) return;
-  const float gp = g[p];
-  const float mp = b1 * m[p] + (1.0f - b1) * gp;
-  const float vp = b2 * v[p] + (1.0f - b2) * gp * gp;
-  m[p] = mp;
-  v[p] = vp;
-  w[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
+  if (p < kMlpParams) adam_update(A, p, g[p]);
 }
 
 // --------------------------------------------------------- BF16 inference
@@ -386,11 +462,23 @@ struct sph_mlp {
   int64_t max_batch;
   hipStream_t s;
   float *w, *g, *m, *v, *mean, *std;
-  float *xs, *z1, *z2, *a2, *sv, *ds, *dz1, *dz2, *lrow, *loss, *loss_acc;
+  float *xs, *z1, *z2, *a2;  // activations the forward pass stores
+  float *part;               // the gradient kernel's block sums
+  float *loss, *loss_acc;
   int64_t step;
 };
 
 namespace {
+
+// Rows per wave and blocks of the gradient kernel for a batch: one wave per
+// row up to 1,024 rows (the chip's SIMDs), then more rows per wave, so that
+// there are at most kGradBlocks block sums (21 KB each).
+constexpr int64_t kGradBlocks = 256;
+
+void grad_split(int64_t B, int &rpw, int &nblk) {
+  rpw = (int)((B + 4 * kGradBlocks - 1) / (4 * kGradBlocks));
+  nblk = (int)((B + 4 * (int64_t)rpw - 1) / (4 * (int64_t)rpw));
+}
 
 size_t mlp_carve(sph_mlp *m, uintptr_t base, int64_t B) {
   uintptr_t off = 0;
@@ -410,37 +498,32 @@ size_t mlp_carve(sph_mlp *m, uintptr_t base, int64_t B) {
   m->z1 = take(B * kMlpHid);
   m->z2 = take(B * kMlpHid);
   m->a2 = take(B * kMlpHid);
-  m->sv = take(B);
-  m->ds = take(B);
-  m->dz1 = take(B * kMlpHid);
-  m->dz2 = take(B * kMlpHid);
-  m->lrow = take(B);
+  m->part = take(std::min<int64_t>(kGradBlocks, (B + 3) / 4) * kPart);  // any batch up to B
   m->loss = take(1);
   m->loss_acc = take(1);
   return off + 256;
 }
 
+// Gradient of rows off .. off + B - 1 (of perm, or of X) into m->g and the
+// mean loss into m->loss; acc != null: also added to (reset: written to) *acc;
+// adam != null: also the parameter update.
 hipError_t mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const float *w, const int32_t *perm, int64_t off,
-                         int64_t B) {
-  hipStream_t s = m->s;
-  const unsigned rb = (unsigned)((B + 3) / 4);
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(rb), dim3(256), 0, s, m->w, m->mean, m->std, X, perm, off, B, m->xs, m->z1, m->z2,
-                     m->a2, m->sv);
-  hipLaunchKernelGGL(k_mlp_loss, dim3(grid_for(B)), dim3(256), 0, s, m->sv, y, w, perm, off, B, m->ds, m->lrow);
-  hipLaunchKernelGGL(k_mlp_bwd_rows, dim3(rb), dim3(256), 0, s, m->w, m->z1, m->z2, m->ds, B, m->dz1, m->dz2);
-  hipLaunchKernelGGL(k_mlp_param_grad, dim3(grid_for(kMlpParams)), dim3(256), 0, s, m->xs, m->z1, m->a2, m->ds, m->dz1,
-                     m->dz2, B, m->g);
-  hipLaunchKernelGGL(k_mlp_loss_sum, dim3(1), dim3(256), 0, s, m->lrow, B, m->loss);
+                         int64_t B, float *acc, int acc_reset, const AdamArgs *adam) {
+  int rpw, nblk;
+  grad_split(B, rpw, nblk);
+  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(256), 0, m->s, m->w, m->mean, m->std, X, y, w, perm, off,
+                     B, rpw, m->part);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kPart + kRedParams - 1) / kRedParams), dim3(kRedParams * kRedSlices), 0, m->s,
+                     m->part, nblk, B, m->g, m->loss, acc, acc_reset, adam ? 1 : 0, adam ? *adam : AdamArgs{});
   return hipGetLastError();
 }
 
-hipError_t mlp_adam(sph_mlp *m, float lr, float b1, float b2, float eps) {
+// The next Adam update's constants (counts the step).
+AdamArgs adam_next(sph_mlp *m, float lr, float b1, float b2, float eps) {
   m->step += 1;
   const float c1 = 1.0f - std::pow(b1, (float)m->step);
   const float c2 = 1.0f - std::pow(b2, (float)m->step);
-  hipLaunchKernelGGL(k_mlp_adam, dim3(grid_for(kMlpParams)), dim3(256), 0, m->s, m->w, m->g, m->m, m->v, lr, b1, b2,
-                     eps, c1, c2);
-  return hipGetLastError();
+  return AdamArgs{m->w, m->m, m->v, lr, b1, b2, eps, c1, c2};
 }
 
 }  // namespace
@@ -525,7 +608,7 @@ sph_status sph_mlp_forward(sph_mlp *m, const float *X, int64_t B, float *logits)
 sph_status sph_mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const float *w, int64_t B, float *loss,
                              float *grad) {
   if (!m || !X || !y || B <= 0 || B > m->max_batch) return SPH_EINVAL;
-  hipError_t e = mlp_loss_grad(m, X, y, w, nullptr, 0, B);
+  hipError_t e = mlp_loss_grad(m, X, y, w, nullptr, 0, B, nullptr, 0, nullptr);
   if (e == hipSuccess && loss) e = hipMemcpyAsync(loss, m->loss, sizeof(float), hipMemcpyDeviceToDevice, m->s);
   if (e == hipSuccess && grad)
     e = hipMemcpyAsync(grad, m->g, sizeof(float) * kMlpParams, hipMemcpyDeviceToDevice, m->s);
@@ -534,7 +617,9 @@ sph_status sph_mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const f
 
 sph_status sph_mlp_adam(sph_mlp *m, float lr, float beta1, float beta2, float eps) {
   if (!m || !(lr > 0) || !(beta1 >= 0 && beta1 < 1) || !(beta2 >= 0 && beta2 < 1) || !(eps > 0)) return SPH_EINVAL;
-  return mlp_adam(m, lr, beta1, beta2, eps) == hipSuccess ? SPH_OK : SPH_EHIP;
+  const AdamArgs A = adam_next(m, lr, beta1, beta2, eps);
+  hipLaunchKernelGGL(k_mlp_adam, dim3(grid_for(kMlpParams)), dim3(256), 0, m->s, m->g, A);
+  return hipGetLastError() == hipSuccess ? SPH_OK : SPH_EHIP;
 }
 
 sph_status sph_mlp_train_epoch(sph_mlp *m, const float *X, const float *y, const float *w, const int32_t *perm,
@@ -544,12 +629,8 @@ sph_status sph_mlp_train_epoch(sph_mlp *m, const float *X, const float *y, const
   int64_t nb = 0;
   for (int64_t off = 0; off < n; off += batch) {
     const int64_t B = std::min(batch, n - off);
-    hipError_t e = mlp_loss_grad(m, X, y, w, perm, off, B);
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_mlp_loss_acc, dim3(1), dim3(1), 0, m->s, m->loss, m->loss_acc, nb == 0 ? 1 : 0);
-      e = mlp_adam(m, lr, 0.9f, 0.999f, 1e-8f);
-    }
-    if (e != hipSuccess) return SPH_EHIP;
+    const AdamArgs A = adam_next(m, lr, 0.9f, 0.999f, 1e-8f);
+    if (mlp_loss_grad(m, X, y, w, perm, off, B, m->loss_acc, nb == 0 ? 1 : 0, &A) != hipSuccess) return SPH_EHIP;
     ++nb;
   }
   if (mean_loss) {
