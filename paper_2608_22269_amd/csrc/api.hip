@@ -1221,94 +1221,69 @@ extern "C" sph_status sph_fields(sph_ctx *c, int32_t field, void *out, int32_t o
   double *dd = (double *)dst;
   int32_t *di = (int32_t *)dst;
   const uint32_t *fid = c->mixed ? c->mcur.id : c->cur.id;
-  // zero first for fields that only fluid rows define
-  if (rate_field || field == SPH_FIELD_MIRROR_SRC) {
-    if (fs.elem == 8) e = launch_fill_f64(dd, 0.0, c->n * fs.width, s);
-    else hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->n * fs.width)), dim3(kBlock), 0, s, di,
-                            field == SPH_FIELD_MIRROR_SRC ? -1 : 0, c->n * fs.width);
-  }
+  const uint32_t *did = c->dm.id;
+  const uint32_t nout = (uint32_t)c->n;
+  auto rows = [&](const RowSrc &f, const RowSrc &d, int width) {
+    return launch_export_rows(f, fid, nf, d, did, nd, width, dd, s, nout);
+  };
+  auto words = [&](const void *src, uint32_t mask, int shift, int width) {
+    return launch_export_u32((const uint32_t *)src, mask, shift, width, fid, nf, did, nd, (uint32_t *)dst, s, nout);
+  };
+  const RowSrc zero{};
+  auto soa = [&](double *const *p, int width) {
+    return RowSrc{{p[0], width > 1 ? p[1] : nullptr, width > 2 ? p[2] : nullptr}, nullptr, 0};
+  };
+  auto one = [](const double *p) { return RowSrc{{p, nullptr, nullptr}, nullptr, 0}; };
+  auto rec = [](const double4 *p, int comp) { return RowSrc{{nullptr, nullptr, nullptr}, p, comp}; };
   if (c->mixed && (field == SPH_FIELD_X || field == SPH_FIELD_U || field == SPH_FIELD_PHI || field == SPH_FIELD_RHO ||
                    field == SPH_FIELD_P || field == SPH_FIELD_MASS || field == SPH_FIELD_CELL)) {
-    e = launch_fields_mixed(c->P, c->g, c->mcur, nf, field, dst, s, (uint32_t)c->n);
+    e = launch_fields_mixed(c->P, c->g, c->mcur, nf, field, dst, s, nout);
+    if (e == hipSuccess && (field == SPH_FIELD_X || field == SPH_FIELD_MASS))
+      e = launch_export_rows(zero, fid, 0, field == SPH_FIELD_X ? soa(c->dm.x, dim) : one(c->dm.m), did, nd,
+                             field == SPH_FIELD_X ? dim : 1, dd, s, nout);
+    if (e == hipSuccess && (field == SPH_FIELD_U || field == SPH_FIELD_PHI || field == SPH_FIELD_RHO || field == SPH_FIELD_P))
+      e = launch_dummy_fields_mixed(c->P, c->mrec, nf, did, nd, field, dst, s, nout);
   } else {
     switch (field) {
-      case SPH_FIELD_X:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->cur.x[a], fid, nf, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_U:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->cur.u[a], fid, nf, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_PHI: e = launch_gather_f64(c->cur.phi, fid, nf, dd, 1, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_MASS: e = launch_gather_f64(c->cur.m, fid, nf, dd, 1, 0, s, (uint32_t)c->n); break;
+      case SPH_FIELD_X: e = rows(soa(c->cur.x, dim), soa(c->dm.x, dim), dim); break;
+      case SPH_FIELD_U: e = rows(soa(c->cur.u, dim), rec(c->rec1 + nf, 0), dim); break;
+      case SPH_FIELD_PHI: e = rows(one(c->cur.phi), rec(c->rec0 + nf, 3), 1); break;
+      case SPH_FIELD_MASS: e = rows(one(c->cur.m), one(c->dm.m), 1); break;
       case SPH_FIELD_RHO: case SPH_FIELD_P:
-        e = launch_rho_p(c->P, c->cur.phi, fid, nf, dd, field == SPH_FIELD_RHO ? 0 : 1, s, (uint32_t)c->n);
+        e = launch_rho_p(c->P, c->cur.phi, fid, nf, dd, field == SPH_FIELD_RHO ? 0 : 1, s, nout);
+        if (e == hipSuccess) e = launch_rho_p_rec(c->P, c->rec0 + nf, did, nd, dd, field == SPH_FIELD_RHO ? 0 : 1, s, nout);
         break;
       case SPH_FIELD_CELL: {
         const double *xx[3] = {c->cur.x[0], c->cur.x[1], c->cur.x[2]};
-        e = launch_cells_of(c->g, dim, xx, fid, nf, di, s, (uint32_t)c->n);
+        e = launch_cells_of(c->g, dim, xx, fid, nf, di, s, nout);
         break;
       }
-      default: break;
-    }
-  }
-  // dummy rows of state fields
-  if (e == hipSuccess) {
-    switch (field) {
-      case SPH_FIELD_X:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->dm.x[a], c->dm.id, nd, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_MASS: e = launch_gather_f64(c->dm.m, c->dm.id, nd, dd, 1, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_CELL: {
-        const double *xx[3] = {c->dm.x[0], c->dm.x[1], c->dm.x[2]};
-        e = launch_cells_of(c->g, dim, xx, c->dm.id, nd, di, s, (uint32_t)c->n);
-        break;
-      }
-      case SPH_FIELD_U:
-        if (!c->mixed) e = launch_gather_rec(c->rec1 + nf, c->dm.id, nd, dd, dim, 0, dim, s, (uint32_t)c->n);
-        else e = launch_dummy_fields_mixed(c->P, c->mrec, nf, c->dm.id, nd, field, dst, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_PHI:
-        if (!c->mixed) e = launch_gather_rec(c->rec0 + nf, c->dm.id, nd, dd, 1, 3, 1, s, (uint32_t)c->n);
-        else e = launch_dummy_fields_mixed(c->P, c->mrec, nf, c->dm.id, nd, field, dst, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_RHO: case SPH_FIELD_P:
-        if (!c->mixed) e = launch_rho_p_rec(c->P, c->rec0 + nf, c->dm.id, nd, dd, field == SPH_FIELD_RHO ? 0 : 1, s, (uint32_t)c->n);
-        else e = launch_dummy_fields_mixed(c->P, c->mrec, nf, c->dm.id, nd, field, dst, s, (uint32_t)c->n);
+      // rates: zero for dummies
+      case SPH_FIELD_DUDT: e = rows(soa(c->r.acc, dim), zero, dim); break;
+      case SPH_FIELD_DELTA_U: e = rows(soa(c->r.dus, dim), zero, dim); break;
+      case SPH_FIELD_NORMAL: e = rows(soa(c->r.nrm, dim), zero, dim); break;
+      case SPH_FIELD_LAMBDA: e = rows(soa(c->r.lam, 3), zero, 3); break;
+      case SPH_FIELD_DPHIDT: e = rows(one(c->r.dphi), zero, 1); break;
+      case SPH_FIELD_FS: e = words(c->r.flags, kFlagFS, 1, 1); break;
+      case SPH_FIELD_TIC: e = words(c->r.flags, kFlagCons, 0, 1); break;
+      case SPH_FIELD_NNB: e = words(c->r.nnb, 0xffffffffu, 0, 1); break;
+      case SPH_FIELD_FEATURES: e = words(c->r.feat, 0xffffffffu, 0, kNFeat); break;
+      case SPH_FIELD_LOGIT: e = words(c->r.logit, 0xffffffffu, 0, 1); break;
+      case SPH_FIELD_FS_PATH:
+        if (c->n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->n)), dim3(kBlock), 0, s, di, 0, c->n);
+        if (nf > 0) hipLaunchKernelGGL(k_path_of, dim3(grid_for(nf)), dim3(kBlock), 0, s, c->r.flags, fid, nf, di, nout);
         break;
       case SPH_FIELD_MIRROR_SRC:
+        if (c->n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->n)), dim3(kBlock), 0, s, di, -1, c->n);
         if (nd > 0)
-          hipLaunchKernelGGL(k_mirror_src_ids, dim3(grid_for(nd)), dim3(kBlock), 0, s, c->dm.src, c->dm.id, fid, nd, di,
-                             (uint32_t)c->n);
+          hipLaunchKernelGGL(k_mirror_src_ids, dim3(grid_for(nd)), dim3(kBlock), 0, s, c->dm.src, did, fid, nd, di, nout);
         break;
       default: break;
     }
   }
-  // rate fields (fluid rows)
-  if (e == hipSuccess && rate_field) {
-    switch (field) {
-      case SPH_FIELD_DUDT:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->r.acc[a], fid, nf, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_DELTA_U:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->r.dus[a], fid, nf, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_NORMAL:
-        for (int a = 0; a < dim && e == hipSuccess; ++a) e = launch_gather_f64(c->r.nrm[a], fid, nf, dd, dim, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_LAMBDA:
-        for (int a = 0; a < 3 && e == hipSuccess; ++a) e = launch_gather_f64(c->r.lam[a], fid, nf, dd, 3, a, s, (uint32_t)c->n);
-        break;
-      case SPH_FIELD_DPHIDT: e = launch_gather_f64(c->r.dphi, fid, nf, dd, 1, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_FS: e = launch_gather_u32_bits(c->r.flags, fid, nf, di, kFlagFS, 1, s, (uint32_t)c->n); break;
-      case SPH_FIELD_TIC: e = launch_gather_u32_bits(c->r.flags, fid, nf, di, kFlagCons, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_NNB: e = launch_gather_u32_bits(c->r.nnb, fid, nf, di, 0xffffffffu, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_FEATURES: e = launch_gather_rows_f32(c->r.feat, fid, nf, kNFeat, (float *)dst, s, (uint32_t)c->n); break;
-      case SPH_FIELD_LOGIT: e = launch_gather_u32_bits((const uint32_t *)c->r.logit, fid, nf, di, 0xffffffffu, 0, s, (uint32_t)c->n); break;
-      case SPH_FIELD_FS_PATH:
-        if (nf > 0) hipLaunchKernelGGL(k_path_of, dim3(grid_for(nf)), dim3(kBlock), 0, s, c->r.flags, fid, nf, di, (uint32_t)c->n);
-        break;
-      default: break;
-    }
+  if (e == hipSuccess && field == SPH_FIELD_CELL) {
+    const double *xx[3] = {c->dm.x[0], c->dm.x[1], c->dm.x[2]};
+    e = launch_cells_of(c->g, dim, xx, did, nd, di, s, nout);
   }
   if (e == hipSuccess) e = hipGetLastError();
   sph_status st = hip_check(c, e, "fields");

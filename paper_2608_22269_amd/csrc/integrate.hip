@@ -232,54 +232,52 @@ hipError_t launch_stage_f64(const Phys &P, const FluidF64 &f, const Rates &r, in
 
 // ---------------------------------------------------------------- gathers
 
-__global__ void k_gather_f64(const double *__restrict__ src, const uint32_t *__restrict__ id, int64_t n,
-                             double *__restrict__ dst, int stride, int comp, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n && id[k] < nout) dst[(int64_t)id[k] * stride + comp] = src[k];
+// One row of W doubles per particle, in the caller's order: fluid row k to
+// row fid[k], dummy row k to row did[k].  All components of a row are written
+// by one thread: a launch per component and particle kind wrote every line of
+// the output several times (x, U and phi of 17.5M fluid and 2.0M wall
+// particles: 2.5 ms against 1.1 ms, bound by the scattered lines).
+template <int W>
+__device__ __forceinline__ void export_row(const RowSrc &r, int64_t k, double *dst) {
+  double v[W];
+#pragma unroll
+  for (int a = 0; a < W; ++a) v[a] = 0.0;
+  if (r.rec) {
+    const double4 q = r.rec[k];
+    const double c[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int a = 0; a < W; ++a) v[a] = r.comp == 0 ? c[a] : c[3];
+  } else if (r.c[0]) {
+#pragma unroll
+    for (int a = 0; a < W; ++a) v[a] = r.c[a][k];
+  }
+#pragma unroll
+  for (int a = 0; a < W; ++a) dst[a] = v[a];
 }
 
-__global__ void k_gather_f32_as_f64(const float *__restrict__ src, const uint32_t *__restrict__ id, int64_t n,
-                                    double *__restrict__ dst, int stride, int comp, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n && id[k] < nout) dst[(int64_t)id[k] * stride + comp] = (double)src[k];
+template <int W>
+__global__ void __launch_bounds__(256) k_export_rows(RowSrc f, const uint32_t *__restrict__ fid, int64_t nf, RowSrc d,
+                                                     const uint32_t *__restrict__ did, int64_t nd,
+                                                     double *__restrict__ dst, uint32_t nout) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nf + nd) return;
+  const uint32_t id = k < nf ? fid[k] : did[k - nf];
+  if (id >= nout) return;
+  if (k < nf) export_row<W>(f, k, dst + (int64_t)id * W);
+  else export_row<W>(d, k - nf, dst + (int64_t)id * W);
 }
 
-__global__ void k_gather_rec(const double4 *__restrict__ rec, const uint32_t *__restrict__ id, int64_t n,
-                             double *__restrict__ dst, int stride, int comp, int ncomp, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n || id[k] >= nout) return;
-  double4 v = rec[k];
-  double c[4] = {v.x, v.y, v.z, v.w};
-  for (int a = 0; a < ncomp; ++a) dst[(int64_t)id[k] * stride + a] = c[comp + a];
-}
-
-__global__ void k_gather_u32_bits(const uint32_t *__restrict__ src, const uint32_t *__restrict__ id, int64_t n,
-                                  int32_t *__restrict__ dst, uint32_t mask, int shift, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n && id[k] < nout) dst[id[k]] = (int32_t)((src[k] & mask) >> shift);
-}
-
-__global__ void k_gather_i32(const int32_t *__restrict__ src, const uint32_t *__restrict__ id, int64_t n,
-                             int32_t *__restrict__ dst, int stride, int comp, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n && id[k] < nout) dst[(int64_t)id[k] * stride + comp] = src[k];
-}
-
-__global__ void k_gather_rows_f32(const float *__restrict__ src, const uint32_t *__restrict__ id, int64_t n,
-                                  int width, float *__restrict__ dst, uint32_t nout) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n || id[k] >= nout) return;
-  for (int c = 0; c < width; ++c) dst[(int64_t)id[k] * width + c] = src[k * width + c];
-}
-
-__global__ void k_fill_f64(double *p, double v, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-__global__ void k_fill_f32(float *p, float v, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// width words per fluid particle, (src & mask) >> shift; zeros for dummies.
+__global__ void __launch_bounds__(256) k_export_u32(const uint32_t *__restrict__ src, uint32_t mask, int shift,
+                                                    int width, const uint32_t *__restrict__ fid, int64_t nf,
+                                                    const uint32_t *__restrict__ did, int64_t nd,
+                                                    uint32_t *__restrict__ dst, uint32_t nout) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = t / width;
+  if (k >= nf + nd) return;
+  const uint32_t id = k < nf ? fid[k] : did[k - nf];
+  if (id >= nout) return;
+  dst[(int64_t)id * width + (t - k * width)] = k < nf ? (src[t] & mask) >> shift : 0u;
 }
 
 template <int DIM>
@@ -311,57 +309,26 @@ __global__ void k_rho_p_rec(Phys P, const double4 *__restrict__ rec, const uint3
   dst[id[k]] = which == 0 ? rho : P.c0 * P.c0 * (rho - P.rho0);
 }
 
-hipError_t launch_gather_f64(const double *src, const uint32_t *id, int64_t n, double *dst, int stride, int comp,
-                             hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_f64, dim3(grid_for(n)), dim3(kBlock), 0, s, src, id, n, dst, stride, comp, nout);
+hipError_t launch_export_rows(const RowSrc &f, const uint32_t *fid, int64_t nf, const RowSrc &d, const uint32_t *did,
+                              int64_t nd, int width, double *dst, hipStream_t s, uint32_t nout) {
+  if (nf + nd <= 0) return hipSuccess;
+  const dim3 gr(grid_for(nf + nd)), bl(kBlock);
+  if (width == 1)
+    hipLaunchKernelGGL(k_export_rows<1>, gr, bl, 0, s, f, fid, nf, d, did, nd, dst, nout);
+  else if (width == 2)
+    hipLaunchKernelGGL(k_export_rows<2>, gr, bl, 0, s, f, fid, nf, d, did, nd, dst, nout);
+  else if (width == 3)
+    hipLaunchKernelGGL(k_export_rows<3>, gr, bl, 0, s, f, fid, nf, d, did, nd, dst, nout);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_gather_f32_as_f64(const float *src, const uint32_t *id, int64_t n, double *dst, int stride,
-                                    int comp, hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_f32_as_f64, dim3(grid_for(n)), dim3(kBlock), 0, s, src, id, n, dst, stride, comp, nout);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_rec(const double4 *rec, const uint32_t *id, int64_t n, double *dst, int stride, int comp,
-                             int ncomp, hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_rec, dim3(grid_for(n)), dim3(kBlock), 0, s, rec, id, n, dst, stride, comp, ncomp, nout);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_u32_bits(const uint32_t *src, const uint32_t *id, int64_t n, int32_t *dst, uint32_t mask,
-                                  int shift, hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_u32_bits, dim3(grid_for(n)), dim3(kBlock), 0, s, src, id, n, dst, mask, shift, nout);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_i32(const int32_t *src, const uint32_t *id, int64_t n, int32_t *dst, int stride, int comp,
-                             hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_i32, dim3(grid_for(n)), dim3(kBlock), 0, s, src, id, n, dst, stride, comp, nout);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_rows_f32(const float *src, const uint32_t *id, int64_t n, int width, float *dst,
-                                  hipStream_t s, uint32_t nout) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_rows_f32, dim3(grid_for(n)), dim3(kBlock), 0, s, src, id, n, width, dst, nout);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(n)), dim3(kBlock), 0, s, p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_f32, dim3(grid_for(n)), dim3(kBlock), 0, s, p, v, n);
+hipError_t launch_export_u32(const uint32_t *src, uint32_t mask, int shift, int width, const uint32_t *fid, int64_t nf,
+                             const uint32_t *did, int64_t nd, uint32_t *dst, hipStream_t s, uint32_t nout) {
+  if (nf + nd <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_export_u32, dim3(grid_for((nf + nd) * width)), dim3(kBlock), 0, s, src, mask, shift, width, fid,
+                     nf, did, nd, dst, nout);
   return hipGetLastError();
 }
 

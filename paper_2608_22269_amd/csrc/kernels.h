@@ -101,20 +101,18 @@ hipError_t launch_stage_f64(const Phys &P, const FluidF64 &f, const Rates &r, in
                             hipStream_t s, double4 *rec0 = nullptr, double4 *rec1 = nullptr, int check = 0);
 hipError_t launch_advance_time(Scalars *sc, hipStream_t s);
 hipError_t launch_set_time(Scalars *sc, double t, hipStream_t s);
-hipError_t launch_gather_f64(const double *src, const uint32_t *id, int64_t n, double *dst, int stride, int comp,
-                             hipStream_t s, uint32_t nout);
-hipError_t launch_gather_f32_as_f64(const float *src, const uint32_t *id, int64_t n, double *dst, int stride,
-                                    int comp, hipStream_t s, uint32_t nout);
-hipError_t launch_gather_rec(const double4 *rec, const uint32_t *id, int64_t n, double *dst, int stride,
-                             int comp, int ncomp, hipStream_t s, uint32_t nout);
-hipError_t launch_gather_u32_bits(const uint32_t *src, const uint32_t *id, int64_t n, int32_t *dst,
-                                  uint32_t mask, int shift, hipStream_t s, uint32_t nout);
-hipError_t launch_gather_i32(const int32_t *src, const uint32_t *id, int64_t n, int32_t *dst, int stride,
-                             int comp, hipStream_t s, uint32_t nout);
-hipError_t launch_gather_rows_f32(const float *src, const uint32_t *id, int64_t n, int width, float *dst,
-                                  hipStream_t s, uint32_t nout);
-hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
-hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s);
+// Field export in the caller's order: a row of 1 to 3 doubles per particle,
+// from component arrays c, from a record's first components (comp 0) or its
+// last one (comp 3), or zeros (neither given); or words.
+struct RowSrc {
+  const double *c[3];
+  const double4 *rec;
+  int comp;
+};
+hipError_t launch_export_rows(const RowSrc &f, const uint32_t *fid, int64_t nf, const RowSrc &d, const uint32_t *did,
+                              int64_t nd, int width, double *dst, hipStream_t s, uint32_t nout);
+hipError_t launch_export_u32(const uint32_t *src, uint32_t mask, int shift, int width, const uint32_t *fid, int64_t nf,
+                             const uint32_t *did, int64_t nd, uint32_t *dst, hipStream_t s, uint32_t nout);
 hipError_t launch_cells_of(const Grid &g, int dim, const double *const x[3], const uint32_t *id, int64_t n,
                            int32_t *dst, hipStream_t s, uint32_t nout);
 hipError_t launch_rho_p(const Phys &P, const double *phi, const uint32_t *id, int64_t n, double *dst, int which,
