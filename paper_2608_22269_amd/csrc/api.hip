@@ -56,7 +56,7 @@ struct sph_ctx {
   MixedRec mrec;
   double4 *rec0, *rec1;  // nf + nd (FP64 path; dummies at nf.. in both paths)
   uint32_t *cs_f, *cs_d;
-  uint32_t *perm;
+  uint2 *perm;
   SortScratch ss;
   Dummies dm;
   Dummies dm2;  // moving body: the dummies' second buffer for their re-sort
@@ -103,6 +103,7 @@ struct sph_ctx {
   bool lists_valid;    // kept lists match the current order (no sort since their build)
   bool umax_fresh;     // sc->umax2_bits holds max |U|^2 of the current state
   bool recs_fresh;     // the neighbour records hold the current state
+  StepPrep prep;       // bookkeeping of the next right-hand side (on: not launched yet)
   bool mixed;
 };
 
@@ -270,7 +271,8 @@ void derive(const sph_params *p, Phys &P, Grid &g) {
   g.NT[0] = kLinearOrder ? 1 : (g.N[1] + kTileY - 1) / kTileY;
   g.NT[1] = kLinearOrder ? 1 : (g.N[2] + kTileZ - 1) / kTileZ;
   const int64_t nb = (int64_t)g.NT[0] * g.NT[1];
-  g.nkey = kLinearOrder ? g.ncell : nb * (int64_t)g.N[0] * kTileY * kTileZ;
+  g.tkeys = (uint32_t)((int64_t)g.N[0] * kTileY * (p->dim == 3 ? kTileZ : 1));
+  g.nkey = kLinearOrder ? g.ncell : nb * (int64_t)g.tkeys;
   g.trank = nullptr;
 }
 
@@ -338,10 +340,12 @@ size_t carve(sph_ctx *c, uintptr_t base, size_t cap) {
   c->cs_f = cv.take<uint32_t>(c->g.nkey + 1);
   c->cs_d = cv.take<uint32_t>(c->g.nkey + 1);
   c->g.trank = cv.take<uint32_t>((int64_t)c->g.NT[0] * c->g.NT[1]);
-  c->perm = cv.take<uint32_t>(nmax);
+  c->perm = cv.take<uint2>(nmax);
   c->ss.key = cv.take<uint32_t>(nmax);
   c->ss.slot = cv.take<uint32_t>(nmax);
   c->ss.count = cv.take<uint32_t>(c->g.nkey + 1);
+  c->ss.tiles = fused_scan_tiles(c->g.nkey);
+  c->ss.tsum = cv.take<uint32_t>(c->ss.tiles);
   c->ss.scan_tmp = cv.take<uint32_t>((int64_t)scan_tmp_words(std::max<int64_t>(c->g.nkey, n + 1)) + 1);
   const bool body = c->p.body_pieces > 0 || c->p.body_free;
   const bool fbody = c->p.body_free != 0;
@@ -430,19 +434,27 @@ struct ProfScope {
 
 // ------------------------------------------------------------ rebuilds
 
+// The next right-hand side's bookkeeping, taken by the launch that runs it.
+StepPrep take_prep(sph_ctx *c) {
+  const StepPrep q = c->prep;
+  c->prep.on = 0;
+  return q;
+}
+
 sph_status rebuild(sph_ctx *c, int with_stage0) {
   ProfScope ps(c, 2);
   hipError_t e;
+  const StepPrep q = take_prep(c);
   if (!c->mixed) {
     e = launch_sort_keys(c->g, c->dim, c->cur.x[0], c->cur.x[1], c->cur.x[2], nullptr, c->nf, c->cur.id, c->ss,
-                         c->cs_f, c->perm, c->sc, c->s);
-    if (e == hipSuccess) e = launch_reorder_f64(c->P, c->perm, c->nf, c->cur, c->alt, c->rec0, c->rec1, with_stage0, c->s);
+                         c->cs_f, c->perm, c->sc, c->s, &c->P, &q);
+    if (e == hipSuccess) e = launch_reorder_f64(c->P, c->ss, c->cs_f, c->perm, c->nf, c->cur, c->alt, c->rec0, c->rec1, with_stage0, c->s);
     std::swap(c->cur, c->alt);
   } else {
     e = launch_sort_keys(c->g, c->dim, nullptr, nullptr, nullptr, c->mcur.cell, c->nf, c->mcur.id, c->ss, c->cs_f,
-                         c->perm, c->sc, c->s);
+                         c->perm, c->sc, c->s, &c->P, &q);
     if (e == hipSuccess)
-      e = launch_reorder_mixed(c->P, c->g, c->perm, c->nf, c->mcur, c->malt, c->mrec, with_stage0, c->s);
+      e = launch_reorder_mixed(c->P, c->g, c->ss, c->cs_f, c->perm, c->nf, c->mcur, c->malt, c->mrec, with_stage0, c->s);
     std::swap(c->mcur, c->malt);
   }
   c->cells_current = true;
@@ -475,17 +487,18 @@ sph_status move_body(sph_ctx *c) {
   if (e == hipSuccess)
     e = launch_sort_keys(c->g, c->dim, c->dm.x[0], c->dm.x[1], c->dm.x[2], nullptr, c->nd, c->dm.id, c->ss, c->cs_d,
                          c->perm, c->sc, c->s);
-  if (e == hipSuccess) e = launch_gather_dummies(c->perm, c->nd, c->dm, c->dm2, c->dim, c->s);
+  if (e == hipSuccess) e = launch_gather_dummies(c->ss, c->cs_d, c->perm, c->nd, c->dm, c->dm2, c->dim, c->s);
   std::swap(c->dm, c->dm2);
   return hip_check(c, e, "body motion");
 }
 
-// One right-hand side.  mode: the pair pass's kPairSearch / kPairSearchKeep /
+// One right-hand side (its bookkeeping in c->prep, unless the sort ran it).  mode: the pair pass's kPairSearch / kPairSearchKeep /
 // kPairKept; win_extra widens the cell searches of the mirror and scan passes
 // (over the cells of the kept lists' build: the bound on any particle's move
 // since).
-sph_status rhs(sph_ctx *c, int stage, int mode = kPairSearch, double win_extra = 0.0) {
-  hipError_t e = launch_stage_time(c->sc, stage, c->s, mode);
+sph_status rhs(sph_ctx *c, int mode = kPairSearch, double win_extra = 0.0) {
+  hipError_t e = hipSuccess;
+  if (c->prep.on) e = launch_prep(c->P, take_prep(c), c->sc, c->s);  // no sort ran it
   if (e == hipSuccess && c->has_body) {
     sph_status sb = move_body(c);
     if (sb != SPH_OK) return sb;
@@ -705,6 +718,7 @@ sph_status sph_init(const sph_params *p, int64_t n, const double *x, const doubl
   c->n_kept = c->n_rebuilt = 0.0;
   c->lists_valid = false;
   c->umax_fresh = c->recs_fresh = false;
+  c->prep = StepPrep{};
   c->profiling = false;
   c->ev_used = 0;
   for (int k = 0; k < 8; ++k) c->prof_ms[k] = c->prof_cnt[k] = 0.0;
@@ -829,11 +843,14 @@ sph_status sph_init(const sph_params *p, int64_t n, const double *x, const doubl
   if (e == hipSuccess)
     e = hipMemcpyAsync((void *)c->g.trank, ranks.data(), sizeof(uint32_t) * ranks.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
+  // what every sort leaves cleared for the next
+  if (e == hipSuccess) e = launch_fill_u32(c->ss.count, 0u, c->g.nkey + 1, s);
+  if (e == hipSuccess) e = launch_fill_u32(c->ss.tsum, 0u, c->ss.tiles, s);
   // dummies: sort once by (cell, original index)
   if (e == hipSuccess && nd > 0) {
     e = launch_sort_keys(c->g, dim, dst.x[0], dst.x[1], dst.x[2], nullptr, nd, dst.id, c->ss, c->cs_d, c->perm, c->sc,
                          s);
-    if (e == hipSuccess) e = launch_gather_dummies(c->perm, nd, dst, c->dm, dim, s);
+    if (e == hipSuccess) e = launch_gather_dummies(c->ss, c->cs_d, c->perm, nd, dst, c->dm, dim, s);
   } else if (e == hipSuccess) {
     e = launch_fill_u32(c->cs_d, 0u, c->g.nkey + 1, s);
   }
@@ -858,7 +875,7 @@ sph_status sph_init(const sph_params *p, int64_t n, const double *x, const doubl
   }
   if (rs == SPH_OK) {
     // mirrored wall values at t = 0, so that fields are defined before any step
-    hipError_t e3 = launch_stage_time(c->sc, 1, s);
+    hipError_t e3 = launch_prep(c->P, StepPrep{1, 0, 1, kPairSearch, 0, 0.0}, c->sc, s);
     if (e3 == hipSuccess && c->has_body) {
       rs = move_body(c);
       if (rs != SPH_OK) e3 = hipErrorUnknown;
@@ -891,8 +908,9 @@ sph_status sph_eval_rates(sph_ctx *c) {
   sph_status st = usable(c);
   if (st != SPH_OK) return st;
   st = umax_of_current(c);
+  c->prep = StepPrep{1, 0, 1, kPairSearch, 0, 0.0};  // max |U| stays for the next step
   if (st == SPH_OK && !c->cells_current) st = rebuild(c, 0);
-  if (st == SPH_OK) st = rhs(c, 1);
+  if (st == SPH_OK) st = rhs(c);
   return st;
 }
 
@@ -903,10 +921,13 @@ sph_status sph_eval_rates(sph_ctx *c) {
 // rounding pad, fits their skin: a pair within 2h now was within 2h + skin
 // at the build.  The bound lives on the device; reading it costs one
 // synchronisation.  Otherwise the stage sorts, searches and builds new lists.
-sph_status stage_rhs(sph_ctx *c, int stage) {
+// Its bookkeeping (at stage 1 with the time step) clears max |U|^2 for the
+// stage update.
+sph_status stage_rhs(sph_ctx *c, int stage, double dt_override) {
+  c->prep = StepPrep{1, stage == 1 ? 1 : 0, stage, kPairSearch, 1, dt_override};
   if (!c->kent) {
     sph_status st = rebuild(c, stage == 2);
-    return st == SPH_OK ? rhs(c, stage) : st;
+    return st == SPH_OK ? rhs(c) : st;
   }
   bool reuse = false;
   double disp = 0.0;
@@ -917,14 +938,15 @@ sph_status stage_rhs(sph_ctx *c, int stage) {
     disp = h.disp;
     reuse = h.vovf == 0u && h.err == 0u && 2.0 * disp + c->P.skin_pad <= c->P.skin_max;
   }
+  c->prep.mode = reuse ? kPairKept : kPairSearchKeep;
   if (reuse) {
     c->n_kept += 1.0;
     sph_status st = refresh(c);
-    return st == SPH_OK ? rhs(c, stage, kPairKept, disp) : st;
+    return st == SPH_OK ? rhs(c, kPairKept, disp) : st;
   }
   c->n_rebuilt += 1.0;
   sph_status st = rebuild(c, stage == 2);
-  if (st == SPH_OK) st = rhs(c, stage, kPairSearchKeep);
+  if (st == SPH_OK) st = rhs(c, kPairSearchKeep);
   if (st == SPH_OK) c->lists_valid = true;
   return st;
 }
@@ -937,9 +959,10 @@ sph_status stage_rhs(sph_ctx *c, int stage) {
 sph_status stage_update(sph_ctx *c, int stage) {
   ProfScope ps(c, 4);
   hipError_t e;
+  const int finish = (c->kent ? kFinishDisp : 0) | (stage == 2 ? kFinishStep : 0);
   const bool recs = c->kent && c->lists_valid && (stage == 1 || (c->p.flags & SPH_F_KEEP_ACROSS_STEPS));
   if (c->mixed)
-    e = launch_stage_mixed(c->P, c->g, c->mcur, c->r, c->nf, c->sc, stage, c->s, recs ? &c->mrec : nullptr);
+    e = launch_stage_mixed(c->P, c->g, c->mcur, c->r, c->nf, c->sc, stage, finish, c->s, recs ? &c->mrec : nullptr);
   else {
     // stage 1 writes the new state into the stage-0 arrays and the roles
     // swap: the state of t^n becomes the stage-0 copy without a copy
@@ -950,25 +973,22 @@ sph_status stage_update(sph_ctx *c, int stage) {
       }
       std::swap(c->cur.phi, c->cur.phi0);
     }
-    e = launch_stage_f64(c->P, c->cur, c->r, c->nf, c->sc, stage, c->s, recs ? c->rec0 : nullptr,
+    e = launch_stage_f64(c->P, c->cur, c->r, c->nf, c->sc, stage, finish, c->s, recs ? c->rec0 : nullptr,
                          recs ? c->rec1 : nullptr, stage == 2 ? 1 : 0);
   }
   c->umax_fresh = true;
   c->recs_fresh = recs;
   if (e == hipSuccess && c->free_body) e = launch_free_body_stage(c->fbody, c->P, c->sc, stage, c->s);
-  if (e == hipSuccess && c->kent) e = launch_disp_add(c->sc, stage, c->s);
-  if (e == hipSuccess && stage == 2) e = launch_advance_time(c->sc, c->s);
   return hip_check(c, e, stage == 1 ? "stage 1" : "stage 2");
 }
 
 // One SSP-RK2 step, launched on c->s.
 sph_status one_step(sph_ctx *c, double dt_override) {
   sph_status st = umax_of_current(c);
-  if (st == SPH_OK) st = hip_check(c, launch_dt(c->P, c->sc, dt_override, c->s), "time step");
-  if (st == SPH_OK) st = stage_rhs(c, 1);
+  if (st == SPH_OK) st = stage_rhs(c, 1, dt_override);
   if (st == SPH_OK) st = stage_update(c, 1);
   if (st == SPH_OK) st = umax_of_current(c);
-  if (st == SPH_OK) st = stage_rhs(c, 2);
+  if (st == SPH_OK) st = stage_rhs(c, 2, dt_override);
   if (st == SPH_OK) st = stage_update(c, 2);
   c->cells_current = false;
   return st;

@@ -80,6 +80,7 @@ struct Grid {
   int64_t ncell;
   int32_t NT[2];     // tiles along y and z
   int64_t nkey;      // number of sort keys (>= ncell)
+  uint32_t tkeys;    // sort keys of a tile: N_x B_y B_z (N_x B_y in 2D, where z = 0)
   const uint32_t *trank;  // Morton rank of every (y, z) tile (NT0 NT1 entries)
 };
 
@@ -88,7 +89,7 @@ __device__ __forceinline__ uint32_t cell_key(const Grid &g, int x, int y, int z)
   if (kLinearOrder) return (uint32_t)(x + (int64_t)y * g.N[0] + (int64_t)z * g.N[0] * g.N[1]);
   const int ty = y / kTileY, tz = z / kTileZ;  // constant powers of two: shifts
   const uint32_t r = g.trank[ty + tz * g.NT[0]];
-  return r * (uint32_t)(g.N[0] * kTileY * kTileZ) +
+  return r * g.tkeys +
          (uint32_t)(x + (y - ty * kTileY) * g.N[0] + (z - tz * kTileZ) * g.N[0] * kTileY);
 }
 
@@ -462,7 +463,7 @@ __device__ __forceinline__ uint32_t walker_key(RowWalker &w, const Grid &g, int 
   const int t = ty + tz * g.NT[0];
   if (t != w.tkey) {
     w.tkey = t;
-    w.tbase = g.trank[t] * (uint32_t)(g.N[0] * kTileY * kTileZ);
+    w.tbase = g.trank[t] * g.tkeys;
   }
   return w.tbase + (uint32_t)(x + (y - ty * kTileY) * g.N[0] + (z - tz * kTileZ) * g.N[0] * kTileY);
 }
@@ -583,6 +584,7 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s);
 // exclusive scan of n u32 values into out (out may alias in); total written
 // to out[n]; tmp needs scan_tmp_words(n) words.
+constexpr int kScanTile = 1024;
 size_t scan_tmp_words(int64_t n);
 hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
 

@@ -157,7 +157,7 @@ __device__ __forceinline__ bool coop_next_row(CoopWalk &w, const Grid &g, const 
       const int t = ty + tz * g.NT[0];
       if (t != w.tkey) {
         w.tkey = t;
-        w.tbase = g.trank[t] * (uint32_t)(g.N[0] * kTileY * kTileZ);
+        w.tbase = g.trank[t] * g.tkeys;
       }
       key0 = w.tbase + (uint32_t)(w.U0 + (iy - ty * kTileY) * g.N[0] + (iz - tz * kTileZ) * g.N[0] * kTileY);
     }

@@ -6,11 +6,15 @@
 // a single digit of log2(ncell) bits: one histogram pass (atomic slot per
 // particle), one exclusive scan over the cells (which *is* the begin/end
 // table), one scatter.  The scatter order inside a cell depends on atomic
-// arrival, so a per-cell pass then sorts each cell's short run by original
-// index: the final order is (HashID, original index), identical to a stable
-// radix sort of the particles in original order, and deterministic.
+// arrival, so the reorder that follows takes each particle's place in its
+// cell from its rank by original index (sorted_place): the final order is
+// (HashID, original index), identical to a stable radix sort of the particles
+// in original order, and deterministic.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
+#include "sorted_place.h"
 
 namespace wb {
 
@@ -42,7 +46,7 @@ hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t 
 // Exclusive scan of u32 in three passes: per-tile sums (tile = 1024), a
 // single-block scan of the tile sums, a per-tile scan that adds the offset.
 
-constexpr int kScanTile = 1024;  // 256 threads x 4 items
+static_assert(kScanTile == 1024, "256 threads x 4 items");
 
 size_t scan_tmp_words(int64_t n) { return (size_t)((n + kScanTile - 1) / kScanTile) + 1; }
 
@@ -92,25 +96,44 @@ __global__ void __launch_bounds__(256) k_scan_sums(uint32_t *sums, int64_t m) {
   if (threadIdx.x == 0) sums[m] = carry;
 }
 
-__global__ void __launch_bounds__(256) k_scan_apply(const uint32_t *__restrict__ in, uint32_t *out,
-                                                    const uint32_t *__restrict__ sums, int64_t n) {
+// CLEAR: the input is zeroed once read (the sort's histogram).  SUMMED: sums
+// holds the plain tile sums and every block adds up those before its own
+// (at most kFusedTiles: 16 loads a thread), which saves the pass over the
+// counts and the one-block pass over the sums.
+constexpr int64_t kFusedTiles = 4096;
+// Particles up to which the hash also adds up the tiles: few tiles hold them
+// all, and beyond, the atomics on those wait for one another longer than a
+// pass over the counts takes (660,000 particles: hash 57 us with them, 10 us
+// and a pass of 4 us without; at 5,000 they cost nothing and save a launch).
+constexpr int64_t kTileAtomics = 32768;
+
+template <bool CLEAR, bool SUMMED>
+__global__ void __launch_bounds__(256) k_scan_apply(uint32_t *in, uint32_t *out, const uint32_t *__restrict__ sums,
+                                                    int64_t n) {
   __shared__ uint32_t sh[4];
   int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * 4;
   uint32_t v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = base + k < n ? in[base + k] : 0;
+  uint32_t before = 0;
+  if (SUMMED) {
+    uint32_t t = 0;
+    for (unsigned k = threadIdx.x; k < blockIdx.x; k += 256) t += sums[k];
+    block_exclusive_scan(t, sh, before);
+  } else {
+    before = sums[blockIdx.x];
+  }
   uint32_t tot;
-  uint32_t ex = block_exclusive_scan(v[0] + v[1] + v[2] + v[3], sh, tot) + sums[blockIdx.x];
+  uint32_t ex = block_exclusive_scan(v[0] + v[1] + v[2] + v[3], sh, tot) + before;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    if (base + k < n) out[base + k] = ex;
+    if (base + k < n) {
+      out[base + k] = ex;
+      if (CLEAR) in[base + k] = 0u;
+    }
     ex += v[k];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    // grand total
-    int64_t m = gridDim.x;
-    out[n] = sums[m];
-  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = before + tot;  // grand total
 }
 
 hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s) {
@@ -118,7 +141,74 @@ hipError_t launch_exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, u
   if (tiles < 1) tiles = 1;
   hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(256), 0, s, in, tmp, n);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, tmp, tiles);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)tiles), dim3(256), 0, s, in, out, tmp, n);
+  hipLaunchKernelGGL((k_scan_apply<false, false>), dim3((unsigned)tiles), dim3(256), 0, s, const_cast<uint32_t *>(in),
+                     out, tmp, n);
+  return hipGetLastError();
+}
+
+int64_t fused_scan_tiles(int64_t nkey) {
+  const int64_t tiles = (nkey + kScanTile - 1) / kScanTile;
+  return tiles <= kFusedTiles ? tiles : 0;
+}
+
+// The begin/end table from the histogram (and its tile sums, if the hash has
+// summed them); clears the histogram.
+static hipError_t scan_counts(const SortScratch &ss, bool summed, uint32_t *start, int64_t nkey, hipStream_t s) {
+  const unsigned tiles = (unsigned)((nkey + kScanTile - 1) / kScanTile);
+  if (ss.tiles) {
+    if (!summed) hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(256), 0, s, ss.count, ss.tsum, nkey);
+    hipLaunchKernelGGL((k_scan_apply<true, true>), dim3(tiles), dim3(256), 0, s, ss.count, start, ss.tsum, nkey);
+  } else {
+    hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(256), 0, s, ss.count, ss.scan_tmp, nkey);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, ss.scan_tmp, (int64_t)tiles);
+    hipLaunchKernelGGL((k_scan_apply<true, false>), dim3(tiles), dim3(256), 0, s, ss.count, start, ss.scan_tmp, nkey);
+  }
+  return hipGetLastError();
+}
+
+// --------------------------------------------------------- step bookkeeping
+
+// dt = CFL min(dx/(C0 + |U|max), dx^2/(2 nu), sqrt(2 dx/|G|max)) at the start
+// of a step (Sec. 2.3); U_max of the stage and the time of its right-hand side
+// (stage 1 at t, stage 2 at t + dt); statistics counters restart.
+__device__ void run_prep(const Phys &P, const StepPrep &q, Scalars *sc) {
+  const double umax = sqrt(__longlong_as_double((long long)sc->umax2_bits));
+  if (q.dt) {
+    double dt = P.dx / (P.c0 + umax);
+    if (P.nu > 0.0) dt = fmin(dt, P.dx * P.dx / (2.0 * P.nu));
+    if (P.gmax > 0.0) dt = fmin(dt, sqrt(2.0 * P.dx / P.gmax));
+    dt *= P.cfl;
+    sc->dt = q.dt_override > 0.0 ? q.dt_override : dt;
+  }
+  if (sc->mode == (uint32_t)kPairKept) {  // statistics of the previous right-hand side by kind
+    sc->pairs_k = sc->pairs;
+    sc->tests_k = sc->tests;
+  } else {
+    sc->pairs_s = sc->pairs;
+    sc->tests_s = sc->tests;
+  }
+  sc->mode = (uint32_t)q.mode;
+  if (q.mode == kPairSearchKeep) {  // this right-hand side builds new kept lists
+    sc->disp = 0.0;
+    sc->vovf = 0u;
+  }
+  sc->umax = umax;
+  sc->t_rhs = q.stage == 2 ? sc->t + sc->dt : sc->t;
+  sc->n_cand = 0;
+  sc->n_scan = 0;
+  sc->n_fs = 0;
+  sc->n_cons = 0;
+  sc->n_sing = 0;
+  sc->n_mlp = 0;
+  sc->pairs = 0ull;
+  sc->tests = 0ull;
+  if (q.reset) sc->umax2_bits = 0ull;
+}
+
+__global__ void k_prep(Phys P, StepPrep q, Scalars *sc) { run_prep(P, q, sc); }
+
+hipError_t launch_prep(const Phys &P, const StepPrep &prep, Scalars *sc, hipStream_t s) {
+  hipLaunchKernelGGL(k_prep, dim3(1), dim3(1), 0, s, P, prep, sc);
   return hipGetLastError();
 }
 
@@ -145,6 +235,19 @@ __device__ __forceinline__ uint32_t reserve_slot(uint32_t *count, uint32_t k, bo
   return base + (uint32_t)(lane - h);
 }
 
+// Adds the wave's particles to the sums of their tiles of sort keys, one
+// atomic per run of lanes in the same tile (as reserve_slot).
+__device__ __forceinline__ void add_tile(uint32_t *tsum, uint32_t k, bool valid) {
+  const int lane = (int)(threadIdx.x & 63);
+  const uint32_t t = k / kScanTile, prev = __shfl_up(t, 1, 64);
+  const unsigned long long vmask = __ballot(valid);
+  const unsigned long long heads = __ballot(valid && (lane == 0 || prev != t));
+  if (!((heads >> lane) & 1ull)) return;
+  const unsigned long long later = heads & ~(lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
+  const int end = later ? __ffsll((long long)later) - 1 : __popcll(vmask);
+  atomicAdd(&tsum[t], (uint32_t)(end - lane));
+}
+
 // Cell of particle i, Eq. (ixyz), its sort key (the cell in the storage
 // order of cell_key), plus its slot inside the cell (arrival order).
 // Out-of-domain or non-finite positions set an error bit and are parked in
@@ -153,8 +256,10 @@ template <int DIM>
 __global__ void __launch_bounds__(256) k_hash_f64(Grid g, const double *__restrict__ x,
                                                   const double *__restrict__ y, const double *__restrict__ z,
                                                   int64_t n, uint32_t *__restrict__ key, uint32_t *__restrict__ slot,
-                                                  uint32_t *__restrict__ count, Scalars *sc) {
+                                                  uint32_t *__restrict__ count, uint32_t *__restrict__ tsum,
+                                                  Scalars *sc, Phys P, StepPrep prep) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (prep.on && i == 0) run_prep(P, prep, sc);  // nothing else here touches these scalars
   const bool valid = i < n;
   double p[3] = {0.0, 0.0, 0.0};
   if (valid) {
@@ -184,6 +289,7 @@ __global__ void __launch_bounds__(256) k_hash_f64(Grid g, const double *__restri
   uint32_t k = 0;
   if (valid && !bad) k = cell_key(g, c[0], c[1], c[2]);
   const uint32_t sl = reserve_slot(count, k, valid);
+  if (tsum) add_tile(tsum, k, valid);
   if (valid) {
     key[i] = k;
     slot[i] = sl;
@@ -193,8 +299,10 @@ __global__ void __launch_bounds__(256) k_hash_f64(Grid g, const double *__restri
 // Mixed path: the cell is stored; the key is computed from it directly.
 __global__ void __launch_bounds__(256) k_hash_packed(Grid g, const uint32_t *__restrict__ cell, int64_t n,
                                                      uint32_t *__restrict__ key, uint32_t *__restrict__ slot,
-                                                     uint32_t *__restrict__ count, Scalars *sc) {
+                                                     uint32_t *__restrict__ count, uint32_t *__restrict__ tsum,
+                                                     Scalars *sc, Phys P, StepPrep prep) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (prep.on && i == 0) run_prep(P, prep, sc);
   const bool valid = i < n;
   const uint32_t c = valid ? cell[i] : 0u;
   const int cx = c & 2047u, cy = (c >> 11) & 2047u, cz = c >> 22;
@@ -205,64 +313,50 @@ __global__ void __launch_bounds__(256) k_hash_packed(Grid g, const uint32_t *__r
     k = cell_key(g, cx, cy, cz);
   }
   const uint32_t sl = reserve_slot(count, k, valid);
+  if (tsum) add_tile(tsum, k, valid);
   if (valid) {
     key[i] = k;
     slot[i] = sl;
   }
 }
 
+// Arrival order of the sorted particles, with their original indices; clears
+// the tile sums for the next sort.
 __global__ void __launch_bounds__(256) k_scatter(const uint32_t *__restrict__ key, const uint32_t *__restrict__ slot,
-                                                 const uint32_t *__restrict__ start, int64_t n,
-                                                 uint32_t *__restrict__ perm) {
+                                                 const uint32_t *__restrict__ start, const uint32_t *__restrict__ id,
+                                                 int64_t n, uint2 *__restrict__ perm, uint32_t *__restrict__ tsum,
+                                                 int64_t tiles) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < tiles) tsum[i] = 0u;
   if (i >= n) return;
-  perm[start[key[i]] + slot[i]] = (uint32_t)i;
-}
-
-// Sorts each cell's run of perm by original index (insertion sort; runs are
-// a few dozen long).  One thread per cell.
-__global__ void __launch_bounds__(256) k_canon(const uint32_t *__restrict__ start, int64_t ncell,
-                                               const uint32_t *__restrict__ id, uint32_t *__restrict__ perm) {
-  int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncell) return;
-  uint32_t b = start[c], e = start[c + 1];
-  // a cell this full only occurs with particles parked after a domain error;
-  // keep arrival order there rather than spend quadratic time
-  if (e - b > 1024u) return;
-  for (uint32_t k = b + 1; k < e; ++k) {
-    uint32_t v = perm[k];
-    uint32_t vid = id[v];
-    uint32_t m = k;
-    while (m > b && id[perm[m - 1]] > vid) {
-      perm[m] = perm[m - 1];
-      --m;
-    }
-    perm[m] = v;
-  }
+  perm[start[key[i]] + slot[i]] = make_uint2((uint32_t)i, id[i]);
 }
 
 hipError_t launch_sort_keys(const Grid &g, int dim, const double *x, const double *y, const double *z,
                             const uint32_t *packed_cell, int64_t n, const uint32_t *id, SortScratch &ss,
-                            uint32_t *start, uint32_t *perm, Scalars *sc, hipStream_t s) {
-  hipError_t e = launch_fill_u32(ss.count, 0u, g.nkey + 1, s);
-  if (e != hipSuccess) return e;
+                            uint32_t *start, uint2 *perm, Scalars *sc, hipStream_t s, const Phys *P,
+                            const StepPrep *prep) {
+  const StepPrep q = prep && P ? *prep : StepPrep{};
+  const Phys ph = P ? *P : Phys{};
+  uint32_t *tsum = ss.tiles && n <= kTileAtomics ? ss.tsum : nullptr;
   if (n > 0) {
     if (packed_cell)
       hipLaunchKernelGGL(k_hash_packed, dim3(grid_for(n)), dim3(kBlock), 0, s, g, packed_cell, n, ss.key, ss.slot,
-                         ss.count, sc);
+                         ss.count, tsum, sc, ph, q);
     else if (dim == 2)
       hipLaunchKernelGGL(k_hash_f64<2>, dim3(grid_for(n)), dim3(kBlock), 0, s, g, x, y, z, n, ss.key, ss.slot,
-                         ss.count, sc);
+                         ss.count, tsum, sc, ph, q);
     else
       hipLaunchKernelGGL(k_hash_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, g, x, y, z, n, ss.key, ss.slot,
-                         ss.count, sc);
+                         ss.count, tsum, sc, ph, q);
+  } else if (q.on) {
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1), 0, s, ph, q, sc);
   }
-  e = launch_exclusive_scan(ss.count, start, g.nkey, ss.scan_tmp, s);
+  hipError_t e = scan_counts(ss, tsum != nullptr, start, g.nkey, s);
   if (e != hipSuccess) return e;
-  if (n > 0) {
-    hipLaunchKernelGGL(k_scatter, dim3(grid_for(n)), dim3(kBlock), 0, s, ss.key, ss.slot, start, n, perm);
-    hipLaunchKernelGGL(k_canon, dim3(grid_for(g.nkey)), dim3(kBlock), 0, s, start, g.nkey, id, perm);
-  }
+  if (n > 0)
+    hipLaunchKernelGGL(k_scatter, dim3(grid_for(std::max(n, ss.tiles))), dim3(kBlock), 0, s, ss.key, ss.slot, start, id,
+                       n, perm, ss.tsum, ss.tiles);
   return hipGetLastError();
 }
 
@@ -273,12 +367,14 @@ hipError_t launch_sort_keys(const Grid &g, int dim, const double *x, const doubl
 // V = m / (rho0 exp(phi / C0^2)).  with_stage0 also carries the stage-0
 // copies (second stage of SSP-RK2).
 template <int DIM>
-__global__ void __launch_bounds__(256) k_reorder_f64(Phys P, const uint32_t *__restrict__ perm, int64_t n,
-                                                     FluidF64 src, FluidF64 dst, double4 *__restrict__ rec0,
+__global__ void __launch_bounds__(256) k_reorder_f64(Phys P, SortScratch ss, const uint32_t *__restrict__ start,
+                                                     const uint2 *__restrict__ perm, int64_t n, FluidF64 src,
+                                                     FluidF64 dst, double4 *__restrict__ rec0,
                                                      double4 *__restrict__ rec1, int with_stage0) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  uint32_t o = perm[k];
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const uint2 from = perm[t];
+  const uint32_t o = from.x, k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
   double xs[3], us[3];
 #pragma unroll
   for (int a = 0; a < DIM; ++a) {
@@ -291,7 +387,7 @@ __global__ void __launch_bounds__(256) k_reorder_f64(Phys P, const uint32_t *__r
   double ph = src.phi[o], m = src.m[o];
   dst.phi[k] = ph;
   dst.m[k] = m;
-  dst.id[k] = src.id[o];
+  dst.id[k] = from.y;
   if (with_stage0) {
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
@@ -305,14 +401,14 @@ __global__ void __launch_bounds__(256) k_reorder_f64(Phys P, const uint32_t *__r
   rec1[k] = make_double4(us[0], us[1], us[2], V);
 }
 
-hipError_t launch_reorder_f64(const Phys &P, const uint32_t *perm, int64_t n, const FluidF64 &src,
-                              const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s) {
+hipError_t launch_reorder_f64(const Phys &P, const SortScratch &ss, const uint32_t *start, const uint2 *perm,
+                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (P.dim == 2)
-    hipLaunchKernelGGL(k_reorder_f64<2>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, perm, n, src, dst, rec0, rec1,
+    hipLaunchKernelGGL(k_reorder_f64<2>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0, rec1,
                        with_stage0);
   else
-    hipLaunchKernelGGL(k_reorder_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, perm, n, src, dst, rec0, rec1,
+    hipLaunchKernelGGL(k_reorder_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0, rec1,
                        with_stage0);
   return hipGetLastError();
 }

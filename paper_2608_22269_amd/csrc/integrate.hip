@@ -7,6 +7,8 @@
 //   - the input split by particle kind at set-up.
 #include "common.h"
 #include "kernels.h"
+#include "sorted_place.h"
+#include "step_scalars.h"
 
 namespace wb {
 
@@ -33,11 +35,6 @@ __global__ void __launch_bounds__(256) k_umax(const T *__restrict__ u0, const T 
 
 __global__ void k_reset_umax(Scalars *sc) { sc->umax2_bits = 0ull; }
 
-hipError_t launch_reset_umax(Scalars *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_umax, dim3(1), dim3(1), 0, s, sc);
-  return hipGetLastError();
-}
-
 hipError_t launch_umax(int dim, const double *const u[3], const float *const uf[3], int64_t nf, Scalars *sc,
                        hipStream_t s) {
   hipLaunchKernelGGL(k_reset_umax, dim3(1), dim3(1), 0, s, sc);
@@ -59,77 +56,6 @@ hipError_t launch_umax(int dim, const double *const u[3], const float *const uf[
   return hipGetLastError();
 }
 
-// dt = CFL min(dx/(C0 + |U|max), dx^2/(2 nu), sqrt(2 dx/|G|max)) at the start
-// of a step (Sec. 2.3); the first right-hand side is evaluated at t.
-__global__ void k_dt(Phys P, Scalars *sc, double dt_override) {
-  double umax = sqrt(__longlong_as_double((long long)sc->umax2_bits));
-  double dt = P.dx / (P.c0 + umax);
-  if (P.nu > 0.0) dt = fmin(dt, P.dx * P.dx / (2.0 * P.nu));
-  if (P.gmax > 0.0) dt = fmin(dt, sqrt(2.0 * P.dx / P.gmax));
-  dt *= P.cfl;
-  sc->dt = dt_override > 0.0 ? dt_override : dt;
-  sc->umax = umax;
-  sc->t_rhs = sc->t;
-}
-
-hipError_t launch_dt(const Phys &P, Scalars *sc, double dt_override, hipStream_t s) {
-  hipLaunchKernelGGL(k_dt, dim3(1), dim3(1), 0, s, P, sc, dt_override);
-  return hipGetLastError();
-}
-
-// Stage bookkeeping: U_max of the stage and the time of its right-hand side
-// (stage 1 at t, stage 2 at t + dt); statistics counters restart.
-__global__ void k_stage_time(Scalars *sc, int stage, int mode) {
-  if (sc->mode == (uint32_t)kPairKept) {  // statistics of the previous right-hand side by kind
-    sc->pairs_k = sc->pairs;
-    sc->tests_k = sc->tests;
-  } else {
-    sc->pairs_s = sc->pairs;
-    sc->tests_s = sc->tests;
-  }
-  sc->mode = (uint32_t)mode;
-  if (mode == kPairSearchKeep) {  // this right-hand side builds new kept lists
-    sc->disp = 0.0;
-    sc->vovf = 0u;
-  }
-  sc->umax = sqrt(__longlong_as_double((long long)sc->umax2_bits));
-  sc->t_rhs = stage == 2 ? sc->t + sc->dt : sc->t;
-  sc->n_cand = 0;
-  sc->n_scan = 0;
-  sc->n_fs = 0;
-  sc->n_cons = 0;
-  sc->n_sing = 0;
-  sc->n_mlp = 0;
-  sc->pairs = 0ull;
-  sc->tests = 0ull;
-}
-
-hipError_t launch_stage_time(Scalars *sc, int stage, hipStream_t s, int mode) {
-  hipLaunchKernelGGL(k_stage_time, dim3(1), dim3(1), 0, s, sc, stage, mode);
-  return hipGetLastError();
-}
-
-// Bound on the move of every particle by the stage update just made (Sec.
-// 2.3), added to sc->disp.  Stage 1: x1 - x0 = dt (U0 + dU0), |U0| <= U_max0
-// and the shifting velocity is clamped to U_max0 / 2, so |x1 - x0| <= 1.5 dt
-// U_max0.  Stage 2: x2 - x1 = (dt (U1 + dU1) - dt (U0 + dU0)) / 2, so
-// |x2 - x1| <= 0.75 dt (U_max0 + U_max1).  The relative margin covers the
-// rounding of the bound and of FP32 velocities.
-__global__ void k_disp_add(Scalars *sc, int stage) {
-  const double dt = sc->dt;
-  if (stage == 1) {
-    sc->umax1 = sc->umax;
-    sc->disp += 1.5 * dt * sc->umax * (1.0 + 1e-6);
-  } else {
-    sc->disp += 0.75 * dt * (sc->umax1 + sc->umax) * (1.0 + 1e-6);
-  }
-}
-
-hipError_t launch_disp_add(Scalars *sc, int stage, hipStream_t s) {
-  hipLaunchKernelGGL(k_disp_add, dim3(1), dim3(1), 0, s, sc, stage);
-  return hipGetLastError();
-}
-
 __global__ void k_set_time(Scalars *sc, double t) {
   sc->t = t;
   sc->t_rhs = t;
@@ -140,13 +66,10 @@ hipError_t launch_set_time(Scalars *sc, double t, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void k_advance_time(Scalars *sc) {
-  sc->t = sc->t + sc->dt;
-  sc->steps += 1.0;
-}
+__global__ void k_finish(Scalars *sc, int stage, int finish) { finish_stage(sc, stage, finish); }
 
-hipError_t launch_advance_time(Scalars *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_advance_time, dim3(1), dim3(1), 0, s, sc);
+hipError_t launch_finish(Scalars *sc, int stage, int finish, hipStream_t s) {
+  if (finish) hipLaunchKernelGGL(k_finish, dim3(1), dim3(1), 0, s, sc, stage, finish);
   return hipGetLastError();
 }
 
@@ -156,17 +79,18 @@ hipError_t launch_advance_time(Scalars *sc, hipStream_t s) {
 // and stage-0 arrays first, so t^n needs no copy) and stage 1 written to the
 // state arrays.  Stage 2: q = 1/2 q0 + 1/2 (q1 + dt rate(q1)) for phi, U, x.
 // Written without contraction, as the equations are printed.  The kernel
-// also folds max |U|^2 of the new state into sc->umax2_bits (reset by the
-// caller), checks the new phi and U for finiteness when asked, and writes the
+// also folds max |U|^2 of the new state into sc->umax2_bits (cleared by the
+// right-hand side's bookkeeping), advances the step's scalars, checks the new phi and U for finiteness when asked, and writes the
 // neighbour records of the new state (rec0 = (x, phi), rec1 = (U, V), as the
 // reorder writes them) when rec0 is given.
 template <int DIM>
 __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, int64_t n, Scalars *sc, int stage,
-                                                   double4 *__restrict__ rec0, double4 *__restrict__ rec1,
-                                                   int check) {
+                                                   int finish, double4 *__restrict__ rec0,
+                                                   double4 *__restrict__ rec1, int check) {
 #pragma clang fp contract(off)
   __shared__ double sh[kBlock / 64];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (finish && i == 0) finish_stage(sc, stage, finish);
   double u2 = 0.0;
   if (i < n) {
     const double dt = sc->dt;
@@ -218,15 +142,14 @@ __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, 
 }
 
 hipError_t launch_stage_f64(const Phys &P, const FluidF64 &f, const Rates &r, int64_t nf, Scalars *sc, int stage,
-                            hipStream_t s, double4 *rec0, double4 *rec1, int check) {
-  hipLaunchKernelGGL(k_reset_umax, dim3(1), dim3(1), 0, s, sc);
-  if (nf <= 0) return hipGetLastError();
+                            int finish, hipStream_t s, double4 *rec0, double4 *rec1, int check) {
+  if (nf <= 0) return launch_finish(sc, stage, finish, s);
   if (P.dim == 2)
-    hipLaunchKernelGGL(k_stage_f64<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, f, r, nf, sc, stage, rec0, rec1,
-                       check);
+    hipLaunchKernelGGL(k_stage_f64<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, f, r, nf, sc, stage, finish, rec0,
+                       rec1, check);
   else
-    hipLaunchKernelGGL(k_stage_f64<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, f, r, nf, sc, stage, rec0, rec1,
-                       check);
+    hipLaunchKernelGGL(k_stage_f64<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, f, r, nf, sc, stage, finish, rec0,
+                       rec1, check);
   return hipGetLastError();
 }
 
@@ -420,17 +343,19 @@ hipError_t launch_split(const Phys &P, int64_t n, const double *x, const double 
   return hipGetLastError();
 }
 
-__global__ void k_gather_dummies(const uint32_t *__restrict__ perm, int64_t nd, Dummies src, Dummies dst, int dim) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nd) return;
-  uint32_t o = perm[k];
+__global__ void k_gather_dummies(SortScratch ss, const uint32_t *__restrict__ start,
+                                 const uint2 *__restrict__ perm, int64_t nd, Dummies src, Dummies dst, int dim) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= nd) return;
+  const uint2 from = perm[t];
+  const uint32_t o = from.x, k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
   for (int a = 0; a < dim; ++a) {
     dst.x[a][k] = src.x[a][o];
     dst.n[a][k] = src.n[a][o];
   }
   dst.m[k] = src.m[o];
   dst.phi_in[k] = src.phi_in[o];
-  dst.id[k] = src.id[o];
+  dst.id[k] = from.y;
   dst.src[k] = -1;
   if (src.mov) {
     dst.mov[k] = src.mov[o];
@@ -440,9 +365,10 @@ __global__ void k_gather_dummies(const uint32_t *__restrict__ perm, int64_t nd, 
     for (int a = 0; a < dim; ++a) dst.n0[a][k] = src.n0[a][o];
 }
 
-hipError_t launch_gather_dummies(const uint32_t *perm, int64_t nd, Dummies src, Dummies dst, int dim, hipStream_t s) {
+hipError_t launch_gather_dummies(const SortScratch &ss, const uint32_t *start, const uint2 *perm, int64_t nd,
+                                 Dummies src, Dummies dst, int dim, hipStream_t s) {
   if (nd <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_dummies, dim3(grid_for(nd)), dim3(kBlock), 0, s, perm, nd, src, dst, dim);
+  hipLaunchKernelGGL(k_gather_dummies, dim3(grid_for(nd)), dim3(kBlock), 0, s, ss, start, perm, nd, src, dst, dim);
   return hipGetLastError();
 }
 

@@ -5,16 +5,34 @@
 
 namespace wb {
 
+// count and, where the scan works from plain tile sums (tiles != 0), tsum are
+// zero between sorts: each sort's scan and scatter clear them.
 struct SortScratch {
-  uint32_t *key, *slot, *count, *scan_tmp;
+  uint32_t *key, *slot, *count, *scan_tmp, *tsum;
+  int64_t tiles;
+};
+
+// Per-right-hand-side bookkeeping on the device, run by one thread of the
+// hash kernel or by a launch of its own (launch_prep): the time step at the
+// start of a step (dt), the stage's time, U_max and counters (stage 1 or 2,
+// mode: the pair pass's), and max |U|^2 cleared for the stage update.
+struct StepPrep {
+  int on, dt, stage, mode, reset;
+  double dt_override;
 };
 
 // grid.hip
+// perm: per arrival place the particle's index before the sort and its
+// original index; the reorders take the places inside the cells from it
 hipError_t launch_sort_keys(const Grid &g, int dim, const double *x, const double *y, const double *z,
                             const uint32_t *packed_cell, int64_t n, const uint32_t *id, SortScratch &ss,
-                            uint32_t *start, uint32_t *perm, Scalars *sc, hipStream_t s);
-hipError_t launch_reorder_f64(const Phys &P, const uint32_t *perm, int64_t n, const FluidF64 &src,
-                              const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s);
+                            uint32_t *start, uint2 *perm, Scalars *sc, hipStream_t s,
+                            const Phys *P = nullptr, const StepPrep *prep = nullptr);
+// tiles of the sort's scan if it works from plain tile sums, else 0
+int64_t fused_scan_tiles(int64_t nkey);
+hipError_t launch_prep(const Phys &P, const StepPrep &prep, Scalars *sc, hipStream_t s);
+hipError_t launch_reorder_f64(const Phys &P, const SortScratch &ss, const uint32_t *start, const uint2 *perm,
+                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s);
 // records of the FP64 state in its current order (no sort)
 hipError_t launch_refresh_f64(const Phys &P, const FluidF64 &f, int64_t n, double4 *rec0, double4 *rec1,
                               hipStream_t s);
@@ -85,21 +103,19 @@ hipError_t launch_sort_rows(const uint32_t *off, int64_t r0, int64_t r1, int32_t
 // integrate.hip
 hipError_t launch_umax(int dim, const double *const u[3], const float *const uf[3], int64_t nf, Scalars *sc,
                        hipStream_t s);
-hipError_t launch_dt(const Phys &P, Scalars *sc, double dt_override, hipStream_t s);
-// stage bookkeeping; mode: the right-hand side's pair-pass mode (kPairSearch,
-// kPairSearchKeep: it builds new kept lists, kPairKept)
-hipError_t launch_stage_time(Scalars *sc, int stage, hipStream_t s, int mode = 0);
-// adds the bound on a particle's move by the stage update just made to sc->disp
-hipError_t launch_disp_add(Scalars *sc, int stage, hipStream_t s);
-// clears sc->umax2_bits (before a kernel that folds max |U|^2 into it)
-hipError_t launch_reset_umax(Scalars *sc, hipStream_t s);
+// what the stage update does to the step's scalars when it is done
+// (kFinishDisp: adds the bound on a particle's move to sc->disp, kFinishStep:
+// advances time)
+constexpr int kFinishDisp = 1, kFinishStep = 2;
 // SSP-RK2 stage update (FP64; stage 1 reads t^n from the stage-0 arrays,
 // which the caller has swapped with the state arrays); also max |U|^2 of the new state into
-// sc->umax2_bits (reset here), a finiteness check of phi and U (check != 0)
+// sc->umax2_bits (cleared by the right-hand side's StepPrep), a finiteness check of phi and U (check != 0)
 // and the neighbour records of the new state (rec0 != nullptr)
 hipError_t launch_stage_f64(const Phys &P, const FluidF64 &f, const Rates &r, int64_t nf, Scalars *sc, int stage,
-                            hipStream_t s, double4 *rec0 = nullptr, double4 *rec1 = nullptr, int check = 0);
-hipError_t launch_advance_time(Scalars *sc, hipStream_t s);
+                            int finish, hipStream_t s, double4 *rec0 = nullptr, double4 *rec1 = nullptr,
+                            int check = 0);
+// the same scalars' update without a fluid particle
+hipError_t launch_finish(Scalars *sc, int stage, int finish, hipStream_t s);
 hipError_t launch_set_time(Scalars *sc, double t, hipStream_t s);
 // Field export in the caller's order: a row of 1 to 3 doubles per particle,
 // from component arrays c, from a record's first components (comp 0) or its
@@ -126,8 +142,8 @@ hipError_t launch_split(const Phys &P, int64_t n, const double *x, const double 
                         const uint32_t *dummy_rank, FluidF64 f, Dummies d, hipStream_t s);
 hipError_t launch_kind_flags(const uint8_t *kind, int64_t n, uint32_t *is_fluid, uint32_t *is_dummy,
                              hipStream_t s);
-hipError_t launch_gather_dummies(const uint32_t *perm, int64_t nd, Dummies src, Dummies dst, int dim,
-                                 hipStream_t s);
+hipError_t launch_gather_dummies(const SortScratch &ss, const uint32_t *start, const uint2 *perm, int64_t nd,
+                                 Dummies src, Dummies dst, int dim, hipStream_t s);
 // Moves the body's dummies to their positions of time sc->t_rhs (x0 + D(t))
 // and stores D and the body velocity in sc->body_x / sc->body_u.
 hipError_t launch_body_move(const Body &B, const Dummies &d, int64_t nd, int dim, Scalars *sc, hipStream_t s);

@@ -18,8 +18,8 @@ struct MixedRec {
 
 hipError_t launch_to_mixed(const Phys &P, const Grid &g, const FluidF64 &src, int64_t nf, const FluidMixed &dst,
                            Scalars *sc, hipStream_t s);
-hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const uint32_t *perm, int64_t nf,
-                                const FluidMixed &src, const FluidMixed &dst, const MixedRec &rec, int with_stage0,
+hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const SortScratch &ss, const uint32_t *start,
+                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst, const MixedRec &rec, int with_stage0,
                                 hipStream_t s);
 hipError_t launch_mirror_mixed(const Phys &P, const Grid &g, const Dummies &d, int64_t nd, const MixedRec &rec,
                                const uint32_t *cs_f, uint32_t nf, const Scalars *sc, hipStream_t s,
@@ -42,10 +42,10 @@ hipError_t launch_scan_mixed(const Phys &P, const Grid &g, const MixedRec &rec, 
                              const uint32_t *cs_d, uint32_t nf, const uint32_t *list, const uint32_t *count,
                              const Rates &out, Scalars *sc, hipStream_t s);
 // SSP-RK2 stage update of the mixed state; also max |U|^2 of the new state
-// into sc->umax2_bits (reset here) and, when rec is given, the neighbour
+// into sc->umax2_bits (cleared by the right-hand side's StepPrep) and, when rec is given, the neighbour
 // records of the new state
 hipError_t launch_stage_mixed(const Phys &P, const Grid &g, const FluidMixed &f, const Rates &r, int64_t nf,
-                              Scalars *sc, int stage, hipStream_t s, const MixedRec *rec = nullptr);
+                              Scalars *sc, int stage, int finish, hipStream_t s, const MixedRec *rec = nullptr);
 // state fields of the fluid rows (x, u, phi, rho, p, mass, cell) in original order
 hipError_t launch_fields_mixed(const Phys &P, const Grid &g, const FluidMixed &f, int64_t nf, int field, void *dst,
                                hipStream_t s, uint32_t nout);

@@ -25,6 +25,8 @@
 #include "mixed.h"
 #include "pair_common.h"
 #include "coop.h"
+#include "sorted_place.h"
+#include "step_scalars.h"
 
 namespace wb {
 
@@ -108,11 +110,14 @@ hipError_t launch_to_mixed(const Phys &P, const Grid &g, const FluidF64 &src, in
 // Gathers the mixed state into HashID order and writes the records:
 // r0 = (offset, cell bits), r1 = (U, V), phi, xa = FP32 absolute position.
 template <int DIM>
-__global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, const uint32_t *__restrict__ perm, int64_t n,
-                                                       FluidMixed src, FluidMixed dst, MixedRec rec, int with_stage0) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  uint32_t o = perm[k];
+__global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, SortScratch ss,
+                                                       const uint32_t *__restrict__ start,
+                                                       const uint2 *__restrict__ perm, int64_t n, FluidMixed src,
+                                                       FluidMixed dst, MixedRec rec, int with_stage0) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const uint2 from = perm[t];
+  const uint32_t o = from.x, k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
   uint32_t c = src.cell[o];
   dst.cell[k] = c;
   float of[3] = {0.f, 0.f, 0.f}, uf[3] = {0.f, 0.f, 0.f};
@@ -132,7 +137,7 @@ __global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, const uin
   dst.phi[k] = ph;
   float m = src.m[o];
   dst.m[k] = m;
-  dst.id[k] = src.id[o];
+  dst.id[k] = from.y;
   if (with_stage0) dst.dphi1[k] = src.dphi1[o];
   float V = (float)((double)m / (P.rho0 * exp(ph * P.inv_c02)));
   int cc[3] = {cell_x(c), cell_y(c), cell_z(c)};
@@ -144,15 +149,15 @@ __global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, const uin
   rec.xa[k] = make_float4(xa[0], xa[1], xa[2], 0.f);
 }
 
-hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const uint32_t *perm, int64_t nf, const FluidMixed &src,
-                                const FluidMixed &dst, const MixedRec &rec, int with_stage0, hipStream_t s) {
+hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const SortScratch &ss, const uint32_t *start,
+                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst, const MixedRec &rec, int with_stage0, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
   if (P.dim == 2)
-    hipLaunchKernelGGL(k_reorder_mixed<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, perm, nf, src, dst, rec,
-                       with_stage0);
+    hipLaunchKernelGGL(k_reorder_mixed<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, ss, start, perm, nf, src, dst,
+                       rec, with_stage0);
   else
-    hipLaunchKernelGGL(k_reorder_mixed<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, perm, nf, src, dst, rec,
-                       with_stage0);
+    hipLaunchKernelGGL(k_reorder_mixed<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, ss, start, perm, nf, src, dst,
+                       rec, with_stage0);
   return hipGetLastError();
 }
 
@@ -904,9 +909,11 @@ hipError_t launch_scan_mixed(const Phys &P, const Grid &g, const MixedRec &rec, 
 
 template <int DIM>
 __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed f, Rates r, int64_t n,
-                                                     Scalars *sc, int stage, MixedRec rec, int write_rec) {
+                                                     Scalars *sc, int stage, int finish, MixedRec rec,
+                                                     int write_rec) {
   __shared__ double sh[kBlock / 64];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (finish && i == 0) finish_stage(sc, stage, finish);
   double u2 = 0.0;
   if (i < n) {
     const double dt = sc->dt;
@@ -988,15 +995,14 @@ __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed 
 }
 
 hipError_t launch_stage_mixed(const Phys &P, const Grid &g, const FluidMixed &f, const Rates &r, int64_t nf,
-                              Scalars *sc, int stage, hipStream_t s, const MixedRec *rec) {
-  hipError_t e = launch_reset_umax(sc, s);
-  if (e != hipSuccess || nf <= 0) return e;
+                              Scalars *sc, int stage, int finish, hipStream_t s, const MixedRec *rec) {
+  if (nf <= 0) return launch_finish(sc, stage, finish, s);
   const MixedRec rr = rec ? *rec : MixedRec{nullptr, nullptr, nullptr, nullptr};
   if (P.dim == 2)
-    hipLaunchKernelGGL(k_stage_mixed<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, f, r, nf, sc, stage, rr,
+    hipLaunchKernelGGL(k_stage_mixed<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, f, r, nf, sc, stage, finish, rr,
                        rec ? 1 : 0);
   else
-    hipLaunchKernelGGL(k_stage_mixed<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, f, r, nf, sc, stage, rr,
+    hipLaunchKernelGGL(k_stage_mixed<3>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, f, r, nf, sc, stage, finish, rr,
                        rec ? 1 : 0);
   return hipGetLastError();
 }
