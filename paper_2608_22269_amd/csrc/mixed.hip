@@ -25,6 +25,7 @@
 #include "mixed.h"
 #include "pair_common.h"
 #include "coop.h"
+#include "nearest.h"
 #include "sorted_place.h"
 #include "step_scalars.h"
 
@@ -199,47 +200,35 @@ hipError_t launch_refresh_mixed(const Phys &P, const Grid &g, const FluidMixed &
 // Dummy records of the mixed path (Sec. 2.4): nearest fluid particle within
 // 2h by the FP32 test (ties -> lower original index); phi_d = phi_f +
 // G.(x_d - x_f) with both positions in FP64; slip velocity; V_d = m_d/rho.
-template <int DIM>
+template <int DIM, int T>
 __global__ void __launch_bounds__(256) k_mirror_mixed(Phys P, Grid g, Dummies d, int64_t nd, MixedRec rec,
                                                       const uint32_t *__restrict__ cs_f, uint32_t nf,
                                                       const Scalars *__restrict__ sc,
                                                       const uint32_t *__restrict__ fid) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nd) return;
+  constexpr int kRows = kBlock / T;
+  __shared__ int64_t found[kRows];
+  const int64_t first = (int64_t)blockIdx.x * kRows;
+  {
+    const int row = (int)threadIdx.x / T;
+    const int64_t k = min(first + row, nd - 1);
+    const double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
+    const float xf = (float)xd, yf = (float)yd, zf = (float)zd;
+    RowWalker w;
+    walker_init<DIM>(w, g, xd, yd, zd, P.win);
+    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, (float)P.two_h2, [&](uint32_t q) {
+      const float4 b = rec.xa[q];
+      const float dxv = b.x - xf, dyv = b.y - yf, dzv = DIM == 3 ? b.z - zf : 0.f;
+      const float s = fmaf(dxv, dxv, dyv * dyv);
+      return DIM == 3 ? fmaf(dzv, dzv, s) : s;
+    });
+    if ((threadIdx.x & (T - 1)) == 0) found[row] = j;
+  }
+  __syncthreads();
+  const int64_t k = first + threadIdx.x;
+  if (threadIdx.x >= kRows || k >= nd) return;
+  const int64_t best = found[threadIdx.x];
   const double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
   const float xf = (float)xd, yf = (float)yd, zf = (float)zd;
-  const float two_h2 = (float)P.two_h2;
-  RowWalker w;
-  walker_init<DIM>(w, g, xd, yd, zd, P.win);
-  int64_t best = -1;
-  uint32_t best_id = 0;
-  float best_r2 = 0.f;
-  auto test_run = [&](uint32_t a, uint32_t e) {
-    for (uint32_t j = a; j < e; ++j) {
-      float4 b = rec.xa[j];
-      float dxv = b.x - xf, dyv = b.y - yf, dzv = DIM == 3 ? b.z - zf : 0.f;
-      float r2 = dxv * dxv + dyv * dyv + dzv * dzv;
-      if (r2 <= two_h2) {
-        uint32_t jid = fid[j];
-        if (best < 0 || r2 < best_r2 || (r2 == best_r2 && jid < best_id)) {
-          best = j;
-          best_r2 = r2;
-          best_id = jid;
-        }
-      }
-    }
-  };
-  // fluid runs, as in the FP64 mirror
-  if (g.reach == 2) {
-    constexpr int NR = DIM == 3 ? 25 : 5;
-    uint32_t lo[NR], hi[NR];
-    walker_fluid_runs<DIM, NR>(w, g, cs_f, lo, hi);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) test_run(lo[r], hi[r]);
-  } else {
-    while (walker_next<DIM>(w, g, cs_f, cs_f, nf))
-      if (w.cur < nf) test_run(w.cur, w.end);
-  }
   d.src[k] = (int32_t)best;
   // static part of the record: cell and offset of the dummy
   int c[3] = {0, 0, 0};
@@ -282,7 +271,10 @@ __global__ void __launch_bounds__(256) k_mirror_mixed(Phys P, Grid g, Dummies d,
     free_body_point_velocity(sc->fb, dr, Uw);
   }
   const float wx = mv ? (float)Uw[0] : 0.f, wy = mv ? (float)Uw[1] : 0.f, wz = mv && DIM == 3 ? (float)Uw[2] : 0.f;
-  const float un = (f1.x - wx) * nx + (f1.y - wy) * ny + (f1.z - wz) * nz;
+  // the fused operations are written out: which ones the compiler forms
+  // depends on the code around, and the dummies' velocities with it
+  const float un = DIM == 3 ? fmaf(f1.z - wz, nz, fmaf(f1.y - wy, ny, (f1.x - wx) * nx))
+                            : fmaf(f1.x - wx, nx, (f1.y - wy) * ny);
   const float V = (float)(d.m[k] / (P.rho0 * exp(phid * P.inv_c02)));
   rec.r1[o] = make_float4(f1.x - un * nx, f1.y - un * ny, DIM == 3 ? f1.z - un * nz : 0.f, V);
   rec.phi[o] = phid;
@@ -292,10 +284,14 @@ hipError_t launch_mirror_mixed(const Phys &P, const Grid &g, const Dummies &d, i
                                const uint32_t *cs_f, uint32_t nf, const Scalars *sc, hipStream_t s,
                                const uint32_t *fid) {
   if (nd <= 0) return hipSuccess;
-  if (P.dim == 2)
-    hipLaunchKernelGGL(k_mirror_mixed<2>, dim3(grid_for(nd)), dim3(kBlock), 0, s, P, g, d, nd, rec, cs_f, nf, sc, fid);
-  else
-    hipLaunchKernelGGL(k_mirror_mixed<3>, dim3(grid_for(nd)), dim3(kBlock), 0, s, P, g, d, nd, rec, cs_f, nf, sc, fid);
+  const bool team = nd <= kMirrorTeamRows;
+#define WB_GO(D, T) \
+  hipLaunchKernelGGL((k_mirror_mixed<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec, cs_f, nf, sc, fid)
+  if (P.dim == 2 && team) WB_GO(2, kMirrorTeam);
+  else if (P.dim == 2) WB_GO(2, 1);
+  else if (team) WB_GO(3, kMirrorTeam);
+  else WB_GO(3, 1);
+#undef WB_GO
   return hipGetLastError();
 }
 

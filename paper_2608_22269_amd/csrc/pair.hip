@@ -21,6 +21,7 @@
 #include "kernels.h"
 #include "pair_common.h"
 #include "coop.h"
+#include "nearest.h"
 
 namespace wb {
 
@@ -48,48 +49,34 @@ static_assert(kBatch <= kRecPad, "batched candidate loads run at most kRecPad re
 
 // ------------------------------------------------------------------ mirror
 
-template <int DIM>
+template <int DIM, int T>
 __global__ void __launch_bounds__(256) k_mirror_f64(Phys P, Grid g, Dummies d, int64_t nd,
                                                     const double4 *__restrict__ rec0,
                                                     const double4 *__restrict__ rec1, double4 *__restrict__ drec0,
                                                     double4 *__restrict__ drec1, const uint32_t *__restrict__ cs_f,
                                                     uint32_t nf, const Scalars *__restrict__ sc,
                                                     const uint32_t *__restrict__ fid) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nd) return;
-  double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
-  RowWalker w;
-  walker_init<DIM>(w, g, xd, yd, zd, P.win);
-  int64_t best = -1;
-  uint32_t best_id = 0;
-  double best_r2 = 0.0;
-  auto test_run = [&](uint32_t a, uint32_t e) {
-    for (uint32_t j = a; j < e; ++j) {
-      double4 b = rec0[j];
-      double r2 = dist2_exact<DIM>(b.x - xd, b.y - yd, b.z - zd);
-      if (r2 <= P.two_h2) {
-        uint32_t jid = fid[j];
-        if (best < 0 || r2 < best_r2 || (r2 == best_r2 && jid < best_id)) {
-          best = j;
-          best_r2 = r2;
-          best_id = jid;
-        }
-      }
-    }
-  };
-  // fluid runs only; at reach 2 the cell starts of all rows are loaded
-  // together (the walk is bound by the latency of its row-by-row loads),
-  // otherwise row by row (pass cs_f twice and skip the dummy runs)
-  if (g.reach == 2) {
-    constexpr int NR = DIM == 3 ? 25 : 5;
-    uint32_t lo[NR], hi[NR];
-    walker_fluid_runs<DIM, NR>(w, g, cs_f, lo, hi);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) test_run(lo[r], hi[r]);
-  } else {
-    while (walker_next<DIM>(w, g, cs_f, cs_f, nf))
-      if (w.cur < nf) test_run(w.cur, w.end);
+  // the nearest particles by teams of lanes, then one lane per wall particle
+  constexpr int kRows = kBlock / T;
+  __shared__ int64_t found[kRows];
+  const int64_t first = (int64_t)blockIdx.x * kRows;
+  {
+    const int row = (int)threadIdx.x / T;
+    const int64_t k = min(first + row, nd - 1);
+    const double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
+    RowWalker w;
+    walker_init<DIM>(w, g, xd, yd, zd, P.win);
+    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, P.two_h2, [&](uint32_t q) {
+      const double4 b = rec0[q];
+      return dist2_exact<DIM>(b.x - xd, b.y - yd, b.z - zd);
+    });
+    if ((threadIdx.x & (T - 1)) == 0) found[row] = j;
   }
+  __syncthreads();
+  const int64_t k = first + threadIdx.x;
+  if (threadIdx.x >= kRows || k >= nd) return;
+  const int64_t best = found[threadIdx.x];
+  const double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
   d.src[k] = (int32_t)best;
   if (best < 0) {
     drec0[k] = make_double4(xd, yd, zd, d.phi_in[k]);
@@ -641,12 +628,14 @@ hipError_t launch_mirror_f64(const Phys &P, const Grid &g, const Dummies &d, int
                              const double4 *rec1, double4 *drec0, double4 *drec1, const uint32_t *cs_f,
                              uint32_t nf, const Scalars *sc, hipStream_t s, const uint32_t *fid) {
   if (nd == 0) return hipSuccess;
-  if (P.dim == 2)
-    hipLaunchKernelGGL(k_mirror_f64<2>, dim3(grid_for(nd)), dim3(kBlock), 0, s, P, g, d, nd, rec0, rec1, drec0, drec1,
-                       cs_f, nf, sc, fid);
-  else
-    hipLaunchKernelGGL(k_mirror_f64<3>, dim3(grid_for(nd)), dim3(kBlock), 0, s, P, g, d, nd, rec0, rec1, drec0, drec1,
-                       cs_f, nf, sc, fid);
+  const bool team = nd <= kMirrorTeamRows;
+#define WB_GO(D, T) \
+  hipLaunchKernelGGL((k_mirror_f64<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec0, rec1, drec0, drec1, cs_f, nf, sc, fid)
+  if (P.dim == 2 && team) WB_GO(2, kMirrorTeam);
+  else if (P.dim == 2) WB_GO(2, 1);
+  else if (team) WB_GO(3, kMirrorTeam);
+  else WB_GO(3, 1);
+#undef WB_GO
   return hipGetLastError();
 }
 
