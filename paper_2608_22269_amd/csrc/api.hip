@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -101,7 +102,7 @@ struct sph_ctx {
   bool cells_current;  // grid/order match the current positions
   bool rates_current;  // rates align with the current order
   bool lists_valid;    // kept lists match the current order (no sort since their build)
-  bool umax_fresh;     // sc->umax2_bits holds max |U|^2 of the current state
+  bool umax_fresh;     // the tallies hold max |U|^2 of the current state
   bool recs_fresh;     // the neighbour records hold the current state
   StepPrep prep;       // bookkeeping of the next right-hand side (on: not launched yet)
   bool mixed;
@@ -584,8 +585,10 @@ sph_status umax_of_current(sph_ctx *c) {
   return hip_check(c, e, "max |U|");
 }
 
-sph_status read_scalars(sph_ctx *c, Scalars *h) {
-  hipError_t e = hipMemcpyAsync(h, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->s);
+// tallies: with the counters of the workgroups, else only what precedes them.
+sph_status read_scalars(sph_ctx *c, Scalars *h, bool tallies = false) {
+  hipError_t e = hipMemcpyAsync(h, c->sc, tallies ? sizeof(Scalars) : offsetof(Scalars, tally), hipMemcpyDeviceToHost,
+                                c->s);
   if (e == hipSuccess) e = hipStreamSynchronize(c->s);
   return hip_check(c, e, "read scalars");
 }
@@ -1081,8 +1084,17 @@ sph_status sph_sync(sph_ctx *c) {
 sph_status sph_stats(sph_ctx *c, double out[20]) {
   if (!c || !out) return SPH_EINVAL;
   Scalars h;
-  sph_status st = read_scalars(c, &h);
+  sph_status st = read_scalars(c, &h, true);
   if (st != SPH_OK) return st;
+  Tally sum{};
+  for (const Tally &t : h.tally) {
+    sum.pairs += t.pairs;
+    sum.tests += t.tests;
+    sum.n_fs += t.n_fs;
+    sum.n_cons += t.n_cons;
+    sum.n_sing += t.n_sing;
+    sum.n_mlp += t.n_mlp;
+  }
   for (int k = 0; k < 20; ++k) out[k] = 0.0;
   out[0] = h.t;
   out[1] = h.dt;
@@ -1090,21 +1102,21 @@ sph_status sph_stats(sph_ctx *c, double out[20]) {
   out[3] = h.umax;
   out[4] = (double)c->nf;
   out[5] = (double)c->nd;
-  out[6] = h.n_fs;
-  out[7] = h.n_cons;
+  out[6] = sum.n_fs;
+  out[7] = sum.n_cons;
   out[8] = c->p.fs_mode == SPH_FS_LEARNED && c->has_clf ? h.n_scan : h.n_cand;
-  out[9] = h.n_mlp;
-  out[10] = h.n_sing;
-  out[11] = (double)h.pairs;
+  out[9] = sum.n_mlp;
+  out[10] = sum.n_sing;
+  out[11] = (double)sum.pairs;
   out[12] = h.n_cand;
-  out[13] = (double)h.tests;
+  out[13] = (double)sum.tests;
   out[14] = c->n_kept;
   out[15] = c->n_rebuilt;
   const bool last_kept = h.mode == (uint32_t)kPairKept;
-  out[16] = (double)(last_kept ? h.pairs_s : h.pairs);
-  out[17] = (double)(last_kept ? h.tests_s : h.tests);
-  out[18] = (double)(last_kept ? h.pairs : h.pairs_k);
-  out[19] = (double)(last_kept ? h.tests : h.tests_k);
+  out[16] = (double)(last_kept ? h.pairs_s : sum.pairs);
+  out[17] = (double)(last_kept ? h.tests_s : sum.tests);
+  out[18] = (double)(last_kept ? sum.pairs : h.pairs_k);
+  out[19] = (double)(last_kept ? sum.tests : h.tests_k);
   return c->status != SPH_OK ? c->status : SPH_OK;
 }
 

@@ -118,19 +118,30 @@ struct Phys {
                           // 2h, wider over the cells of a kept-list build
 };
 
+// Counters that many workgroups add to, one copy per kTallies-th workgroup,
+// each on a cache line of its own: atomics on one address from the eight XCDs
+// take their turns at about 12 ns each (one per workgroup was 0.8 of 0.89 ms of
+// a stage update of 17.5M particles; 2 per wave 93 of the 160 us of the pair
+// pass of 296,000 particles in 2D).  Workgroups go to the XCDs in turn, so with
+// a multiple of eight copies each line stays in one XCD's L2.  run_prep folds
+// and clears them at the start of a right-hand side.
+constexpr int kTallies = 64;
+struct alignas(128) Tally {
+  unsigned long long umax2_bits;  // atomic max of |U|^2 (non-negative double bits)
+  unsigned long long pairs;       // sum of fluid neighbour counts of the last RHS
+  unsigned long long tests;       // candidate distance tests of the last pair pass
+  uint32_t n_fs, n_cons, n_sing, n_mlp;
+};
+
 // Device-resident scalars (one instance in the workspace).
 struct Scalars {
   double t;          // time at the start of the current step
   double dt;         // current step
   double t_rhs;      // time of the right-hand side being evaluated
   double umax;       // sqrt of umax2 for the current right-hand side
-  unsigned long long umax2_bits;  // atomic max of |U|^2 (non-negative double bits)
-  unsigned long long pairs;       // sum of fluid neighbour counts of the last RHS
-  unsigned long long tests;       // candidate distance tests of the last pair pass
   uint32_t err;
   uint32_t n_cand;   // candidates listed by the pair pass
   uint32_t n_scan;   // candidates sent to the scan pass
-  uint32_t n_fs, n_cons, n_sing, n_mlp;
   uint32_t pad_;
   double steps;
   double disp;       // bound on any particle's move since the kept lists were built
@@ -147,7 +158,16 @@ struct Scalars {
   uint32_t fb_on, fb_pad_;
   double fb_c0[3];
   double fb[13], fb0[13], fbF[6];
+  Tally tally[kTallies];
 };
+
+// This workgroup's copy of the counters.
+__device__ __forceinline__ Tally &tally_of(Scalars *sc) { return sc->tally[blockIdx.x % kTallies]; }
+
+// Max of |U|^2 over a workgroup's value b, by one of its threads.
+__device__ __forceinline__ void tally_umax2(Scalars *sc, double b) {
+  atomicMax(&tally_of(sc).umax2_bits, (unsigned long long)__double_as_longlong(b));
+}
 
 // Fluid state, FP64 path, sorted by (cell, original index).
 struct FluidF64 {

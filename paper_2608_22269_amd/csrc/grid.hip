@@ -170,9 +170,23 @@ static hipError_t scan_counts(const SortScratch &ss, bool summed, uint32_t *star
 
 // dt = CFL min(dx/(C0 + |U|max), dx^2/(2 nu), sqrt(2 dx/|G|max)) at the start
 // of a step (Sec. 2.3); U_max of the stage and the time of its right-hand side
-// (stage 1 at t, stage 2 at t + dt); statistics counters restart.
+// (stage 1 at t, stage 2 at t + dt); statistics counters restart.  By one wave:
+// a lane folds and clears each tally, the first does the rest.
 __device__ void run_prep(const Phys &P, const StepPrep &q, Scalars *sc) {
-  const double umax = sqrt(__longlong_as_double((long long)sc->umax2_bits));
+  static_assert(kTallies == 64, "one lane each");
+  Tally &tl = sc->tally[threadIdx.x & 63];
+  const unsigned long long own = tl.umax2_bits;
+  unsigned long long u2 = own, pairs = tl.pairs, tests = tl.tests;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long v = __shfl_xor(u2, o, 64);
+    u2 = v > u2 ? v : u2;
+    pairs += __shfl_xor(pairs, o, 64);
+    tests += __shfl_xor(tests, o, 64);
+  }
+  tl = Tally{q.reset ? 0ull : own, 0ull, 0ull, 0u, 0u, 0u, 0u};
+  if (threadIdx.x != 0) return;
+  const double umax = sqrt(__longlong_as_double((long long)u2));
   if (q.dt) {
     double dt = P.dx / (P.c0 + umax);
     if (P.nu > 0.0) dt = fmin(dt, P.dx * P.dx / (2.0 * P.nu));
@@ -181,11 +195,11 @@ __device__ void run_prep(const Phys &P, const StepPrep &q, Scalars *sc) {
     sc->dt = q.dt_override > 0.0 ? q.dt_override : dt;
   }
   if (sc->mode == (uint32_t)kPairKept) {  // statistics of the previous right-hand side by kind
-    sc->pairs_k = sc->pairs;
-    sc->tests_k = sc->tests;
+    sc->pairs_k = pairs;
+    sc->tests_k = tests;
   } else {
-    sc->pairs_s = sc->pairs;
-    sc->tests_s = sc->tests;
+    sc->pairs_s = pairs;
+    sc->tests_s = tests;
   }
   sc->mode = (uint32_t)q.mode;
   if (q.mode == kPairSearchKeep) {  // this right-hand side builds new kept lists
@@ -196,19 +210,12 @@ __device__ void run_prep(const Phys &P, const StepPrep &q, Scalars *sc) {
   sc->t_rhs = q.stage == 2 ? sc->t + sc->dt : sc->t;
   sc->n_cand = 0;
   sc->n_scan = 0;
-  sc->n_fs = 0;
-  sc->n_cons = 0;
-  sc->n_sing = 0;
-  sc->n_mlp = 0;
-  sc->pairs = 0ull;
-  sc->tests = 0ull;
-  if (q.reset) sc->umax2_bits = 0ull;
 }
 
 __global__ void k_prep(Phys P, StepPrep q, Scalars *sc) { run_prep(P, q, sc); }
 
 hipError_t launch_prep(const Phys &P, const StepPrep &prep, Scalars *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(1), 0, s, P, prep, sc);
+  hipLaunchKernelGGL(k_prep, dim3(1), dim3(64), 0, s, P, prep, sc);
   return hipGetLastError();
 }
 
@@ -259,7 +266,7 @@ __global__ void __launch_bounds__(256) k_hash_f64(Grid g, const double *__restri
                                                   uint32_t *__restrict__ count, uint32_t *__restrict__ tsum,
                                                   Scalars *sc, Phys P, StepPrep prep) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (prep.on && i == 0) run_prep(P, prep, sc);  // nothing else here touches these scalars
+  if (prep.on && i < 64) run_prep(P, prep, sc);  // nothing else here touches these scalars
   const bool valid = i < n;
   double p[3] = {0.0, 0.0, 0.0};
   if (valid) {
@@ -302,7 +309,7 @@ __global__ void __launch_bounds__(256) k_hash_packed(Grid g, const uint32_t *__r
                                                      uint32_t *__restrict__ count, uint32_t *__restrict__ tsum,
                                                      Scalars *sc, Phys P, StepPrep prep) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (prep.on && i == 0) run_prep(P, prep, sc);
+  if (prep.on && i < 64) run_prep(P, prep, sc);
   const bool valid = i < n;
   const uint32_t c = valid ? cell[i] : 0u;
   const int cx = c & 2047u, cy = (c >> 11) & 2047u, cz = c >> 22;

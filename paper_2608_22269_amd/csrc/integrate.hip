@@ -29,15 +29,15 @@ __global__ void __launch_bounds__(256) k_umax(const T *__restrict__ u0, const T 
   __syncthreads();
   if (threadIdx.x == 0) {
     double b = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-    atomicMax(&sc->umax2_bits, (unsigned long long)__double_as_longlong(b));
+    tally_umax2(sc, b);
   }
 }
 
-__global__ void k_reset_umax(Scalars *sc) { sc->umax2_bits = 0ull; }
+__global__ void k_reset_umax(Scalars *sc) { sc->tally[threadIdx.x].umax2_bits = 0ull; }
 
 hipError_t launch_umax(int dim, const double *const u[3], const float *const uf[3], int64_t nf, Scalars *sc,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_umax, dim3(1), dim3(1), 0, s, sc);
+  hipLaunchKernelGGL(k_reset_umax, dim3(1), dim3(kTallies), 0, s, sc);
   if (nf > 0) {
     unsigned blocks = grid_for(nf);
     if (blocks > 1024) blocks = 1024;
@@ -79,10 +79,11 @@ hipError_t launch_finish(Scalars *sc, int stage, int finish, hipStream_t s) {
 // and stage-0 arrays first, so t^n needs no copy) and stage 1 written to the
 // state arrays.  Stage 2: q = 1/2 q0 + 1/2 (q1 + dt rate(q1)) for phi, U, x.
 // Written without contraction, as the equations are printed.  The kernel
-// also folds max |U|^2 of the new state into sc->umax2_bits (cleared by the
-// right-hand side's bookkeeping), advances the step's scalars, checks the new phi and U for finiteness when asked, and writes the
-// neighbour records of the new state (rec0 = (x, phi), rec1 = (U, V), as the
-// reorder writes them) when rec0 is given.
+// also folds max |U|^2 of the new state into the tallies (cleared by the
+// right-hand side's bookkeeping), advances the step's scalars, checks the new
+// phi and U for finiteness when asked, and writes the neighbour records of the
+// new state (rec0 = (x, phi), rec1 = (U, V), as the reorder writes them) when
+// rec0 is given.
 template <int DIM>
 __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, int64_t n, Scalars *sc, int stage,
                                                    int finish, double4 *__restrict__ rec0,
@@ -137,7 +138,7 @@ __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, 
   if (threadIdx.x == 0) {
     double b = sh[0];
     for (int w = 1; w < kBlock / 64; ++w) b = fmax(b, sh[w]);
-    atomicMax(&sc->umax2_bits, (unsigned long long)__double_as_longlong(b));
+    tally_umax2(sc, b);
   }
 }
 

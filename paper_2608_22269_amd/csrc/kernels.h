@@ -12,7 +12,7 @@ struct SortScratch {
   int64_t tiles;
 };
 
-// Per-right-hand-side bookkeeping on the device, run by one thread of the
+// Per-right-hand-side bookkeeping on the device, run by one wave of the
 // hash kernel or by a launch of its own (launch_prep): the time step at the
 // start of a step (dt), the stage's time, U_max and counters (stage 1 or 2,
 // mode: the pair pass's), and max |U|^2 cleared for the stage update.
@@ -109,7 +109,7 @@ hipError_t launch_umax(int dim, const double *const u[3], const float *const uf[
 constexpr int kFinishDisp = 1, kFinishStep = 2;
 // SSP-RK2 stage update (FP64; stage 1 reads t^n from the stage-0 arrays,
 // which the caller has swapped with the state arrays); also max |U|^2 of the new state into
-// sc->umax2_bits (cleared by the right-hand side's StepPrep), a finiteness check of phi and U (check != 0)
+// the tallies (cleared by the right-hand side's StepPrep), a finiteness check of phi and U (check != 0)
 // and the neighbour records of the new state (rec0 != nullptr)
 hipError_t launch_stage_f64(const Phys &P, const FluidF64 &f, const Rates &r, int64_t nf, Scalars *sc, int stage,
                             int finish, hipStream_t s, double4 *rec0 = nullptr, double4 *rec1 = nullptr,

@@ -42,7 +42,7 @@ hipError_t launch_scan_mixed(const Phys &P, const Grid &g, const MixedRec &rec, 
                              const uint32_t *cs_d, uint32_t nf, const uint32_t *list, const uint32_t *count,
                              const Rates &out, Scalars *sc, hipStream_t s);
 // SSP-RK2 stage update of the mixed state; also max |U|^2 of the new state
-// into sc->umax2_bits (cleared by the right-hand side's StepPrep) and, when rec is given, the neighbour
+// into the tallies (cleared by the right-hand side's StepPrep) and, when rec is given, the neighbour
 // records of the new state
 hipError_t launch_stage_mixed(const Phys &P, const Grid &g, const FluidMixed &f, const Rates &r, int64_t nf,
                               Scalars *sc, int stage, int finish, hipStream_t s, const MixedRec *rec = nullptr);

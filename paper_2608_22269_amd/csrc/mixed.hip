@@ -884,7 +884,7 @@ __global__ void __launch_bounds__(256) k_scan_mixed(Phys P, Grid g, MixedRec rec
     if (lane == 0) scan_finish<DIM>(P, out, i, n, covered);
     nfs += covered ? 0u : 1u;
   }
-  if (lane == 0 && nfs) atomicAdd(&sc->n_fs, nfs);
+  if (lane == 0 && nfs) atomicAdd(&tally_of(sc).n_fs, nfs);
 }
 
 hipError_t launch_scan_mixed(const Phys &P, const Grid &g, const MixedRec &rec, const uint32_t *cs_f,
@@ -986,7 +986,7 @@ __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed 
   if (threadIdx.x == 0) {
     double b = sh[0];
     for (int w = 1; w < kBlock / 64; ++w) b = fmax(b, sh[w]);
-    atomicMax(&sc->umax2_bits, (unsigned long long)__double_as_longlong(b));
+    tally_umax2(sc, b);
   }
 }
 

@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(256) k_decide(Phys P, Rates out, const uint32_
     }
     const uint32_t slot = wave_append(&sc->n_scan, on && fb);
     if (on && fb) fallback[slot] = i;
-    wave_count(&sc->n_mlp, on && !fb);
+    wave_count(&tally_of(sc).n_mlp, on && !fb);
     if (on && !fb) {
       uint32_t fl = out.flags[i] | kFlagByMLP;
       if (fs) {
@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(256) k_decide(Phys P, Rates out, const uint32_
       }
       out.flags[i] = fl;
     }
-    wave_count(&sc->n_fs, on && fs);
+    wave_count(&tally_of(sc).n_fs, on && fs);
   }
 }
 

@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(256) k_scan_f64(Phys P, Grid g, const double4 
     if (lane == 0) scan_finish<DIM>(P, out, i, n, covered);
     nfs += covered ? 0u : 1u;
   }
-  if (lane == 0 && nfs) atomicAdd(&sc->n_fs, nfs);
+  if (lane == 0 && nfs) atomicAdd(&tally_of(sc).n_fs, nfs);
 }
 
 hipError_t launch_scan_f64(const Phys &P, const Grid &g, const double4 *rec0, const uint32_t *cs_f,

@@ -191,9 +191,10 @@ __device__ __forceinline__ void pair_epilogue(const Phys &P, Scalars *sc, const 
   const bool cand_l = active && is_cand;
   uint32_t slot = wave_append(&sc->n_cand, cand_l);
   if (cand_l) cand[slot] = i;
-  wave_count(&sc->n_fs, active && (fl & kFlagFS));
-  wave_count(&sc->n_cons, active && cons);
-  wave_count(&sc->n_sing, active && singular);
+  Tally &tl = tally_of(sc);
+  wave_count(&tl.n_fs, active && (fl & kFlagFS));
+  wave_count(&tl.n_cons, active && cons);
+  wave_count(&tl.n_sing, active && singular);
   // ordered-pair and candidate-test counts
   unsigned long long pc = active ? S.nnb : 0, tc = active ? S.ntest : 0;
 #pragma unroll
@@ -201,8 +202,8 @@ __device__ __forceinline__ void pair_epilogue(const Phys &P, Scalars *sc, const 
     pc += __shfl_xor(pc, o, 64);
     tc += __shfl_xor(tc, o, 64);
   }
-  if ((threadIdx.x & 63) == 0 && pc) atomicAdd(&sc->pairs, pc);
-  if ((threadIdx.x & 63) == 0 && tc) atomicAdd(&sc->tests, tc);
+  if ((threadIdx.x & 63) == 0 && pc) atomicAdd(&tl.pairs, pc);
+  if ((threadIdx.x & 63) == 0 && tc) atomicAdd(&tl.tests, tc);
 }
 
 // Scan-region test of neighbour q (squared distance s2 <= (2h)^2) for a
