@@ -524,8 +524,8 @@ sph_status rhs(sph_ctx *c, int mode = kPairSearch, double win_extra = 0.0) {
     }
     if (e == hipSuccess) {
       ProfScope ps(c, mode == kPairKept ? 5 : 0);
-      e = launch_pair_f64(c->P, c->g, c->rec0, c->rec1, c->cs_f, c->cs_d, (uint32_t)c->nf, c->sc, c->r, c->cand, mode,
-                          c->kent, c->kcnt, c->s);
+      e = launch_pair_f64(c->P, c->g, c->rec0, c->rec1, c->cs_f, c->cs_d, (uint32_t)c->nf, c->n, c->sc, c->r, c->cand,
+                          mode, c->kent, c->kcnt, c->s);
     }
   } else {
     if (e == hipSuccess) {

@@ -10,8 +10,9 @@
 //   - the scan-region pass over free-surface candidates;
 //   - neighbour-list export for parity checks.
 //
-// Work mapping.  One lane per fluid particle, particles in storage (sort key)
-// order.  The wave walks the cell rows of Algorithm 1 in lockstep; each lane
+// Work mapping.  Up to some counts a team of 8 lanes per fluid particle
+// (k_pair_team_f64, by_team); beyond them one lane each, particles in storage
+// (sort key) order.  The wave walks the cell rows of Algorithm 1 in lockstep; each lane
 // compacts its in-range candidates into its own column of an LDS list (32
 // entries), and whenever a list may overflow the wave runs the dense pair body
 // over the lists.  Lanes of one wave belong to the same or neighbouring cells,
@@ -337,13 +338,330 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WB_KEP
   pair_epilogue<DIM>(P, sc, out, cand, i, active, S);
 }
 
+// ------------------------------------------------- pair pass by teams
+
+constexpr int kTeam = 8;                   // lanes of a particle
+constexpr int kTeamRows = kBlock / kTeam;  // particles of a block
+
+// DPP controls that exchange lanes l and l ^ O (O = 1, 2: quad_perm) or their
+// mirror images in the half row of 8 lanes (4: row_half_mirror).
+constexpr int dpp_swap(int o) { return o == 1 ? 0xb1 : o == 2 ? 0x4e : 0x141; }
+
+template <int O>
+__device__ __forceinline__ double lane_swap(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), dpp_swap(O), 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), dpp_swap(O), 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Adds N values over the team's lanes and spreads the sums over them: each
+// step halves the values a lane holds (the lanes with bit O clear keep the
+// even ones) and adds the partner's.  The lane's sums are v[0 .. *n), of the
+// values q[0 .. *n).
+template <int O, int N>
+__device__ __forceinline__ void team_reduce(double *v, int sub) {
+  if constexpr (O > 0) {
+    const bool odd = (sub & O) != 0;
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+      const double keep = odd ? v[2 * k + 1] : v[2 * k], send = odd ? v[2 * k] : v[2 * k + 1];
+      v[k] = keep + lane_swap<O>(send);
+    }
+    if (N % 2) v[N / 2] = v[N - 1] + lane_swap<O>(v[N - 1]);
+    team_reduce<O / 2, (N + 1) / 2>(v, sub);
+  }
+}
+template <int O, int N>
+__device__ __forceinline__ int team_slot(int sub, int s) {  // value that slot s of the lane holds
+  if constexpr (O > 0) return min(2 * team_slot<O / 2, (N + 1) / 2>(sub, s) + ((sub & O) ? 1 : 0), N - 1);
+  else return s;
+}
+template <int O, int N>
+constexpr int team_left() {
+  if constexpr (O > 0) return team_left<O / 2, (N + 1) / 2>();
+  else return N;
+}
+
+// Inclusive prefix sum over the lanes of a team (row_shr, cut at the team).
+__device__ __forceinline__ int team_scan(int v, int sub) {
+  int t = __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+  v += sub >= 1 ? t : 0;
+  t = __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += sub >= 2 ? t : 0;
+  t = __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  return v + (sub >= 4 ? t : 0);
+}
+
+// Largest of the wave's team values (equal in a team's lanes), scalar.
+__device__ __forceinline__ int team_max(int v) {
+  int m = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+  for (int l = kTeam; l < 64; l += kTeam) m = max(m, __builtin_amdgcn_readlane(v, l));
+  return m;
+}
+
+// The sums of a particle as a list of the values that its dimension has.
+template <int DIM, class F>
+__device__ __forceinline__ void each_sum(PairSums &S, F f) {
+  int q = 0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    if (DIM == 2 && k != 0 && k != 1 && k != 3) continue;
+    f(S.L[k], q++);
+    f(S.N[k], q++);
+  }
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) {
+    f(S.gs[k], q++);
+    f(S.SR[k], q++);
+    f(S.SC[k], q++);
+    f(S.Ps[k], q++);
+  }
+  f(S.Ds, q++);
+}
+
+// Records below 2^27 (the launch checks it): 32-bit offsets from a scalar base.
+__device__ __forceinline__ const double4 &rec_at(const double4 *rec, uint32_t j) {
+  return *reinterpret_cast<const double4 *>(reinterpret_cast<const char *>(rec) + j * 32u);
+}
+
+// The 8 lanes of a team share a particle.  They compute the windows of eight
+// cell rows side by side, test the windows' records, compact the neighbours
+// into the team's LDS list and run the pair body over it; the sums are added
+// across the team in a fixed tree, and the block's first wave runs the
+// epilogue, a lane per particle.  In 3D over cells of 2h (LONG) a row holds
+// several times eight records and is tested in place; else the windows' record
+// indices are first listed in LDS, so that the short rows fill the lanes (the
+// other way round 928 against 637 us at 651,000 particles, cells of 2h, and 710
+// against 565, cells of h; in 2D both take the same).  Neighbour number n goes to lane n mod 8 wherever the list is
+// emptied, so a plain search, one that keeps its candidates (kPairSearchKeep:
+// radius 2h + skin) and the pass from kept candidates (kPairKept, lists built
+// by this kernel only: full chunks but the last) give the same sums bit for
+// bit.
+// Everything that crosses lanes sits under scalar control flow: trip counts
+// come from ballots and lane reads, and list stores are unconditional (a lane
+// without an entry stores to a spare slot).  A conditional store before a loop
+// that ballots let the compiler run the loop with part of the wave.
+template <int DIM, bool PST4, int MODE, bool LONG>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PST4 ? 4 : 2)))
+k_pair_team_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 *__restrict__ rec1,
+                const uint32_t *__restrict__ cs_f, const uint32_t *__restrict__ cs_d, uint32_t nf, Scalars *sc,
+                Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
+  constexpr bool KEEP = MODE == kPairSearchKeep, KEPT = MODE == kPairKept;
+  constexpr int NS = DIM == 3 ? 25 : 15;
+  constexpr int kPer = LONG ? 3 : 4;                     // records in flight per lane
+  constexpr int kChunk = LONG ? kPer * kTeam : 64;                          // candidates between looks at the list
+  constexpr int kList = KEPT ? kKeepChunks * kPairList : 160;               // list entries of a particle
+  static_assert(kList >= 2 * kChunk, "list entries");
+  __shared__ uint32_t lists[kTeamRows][kList + 1];
+  __shared__ double sums[NS][kTeamRows];
+  __shared__ uint32_t counts[3][kTeamRows];
+  const int sub = (int)(threadIdx.x & (kTeam - 1)), team = (int)threadIdx.x / kTeam;
+  const bool upper = (threadIdx.x & 32u) != 0u;
+  const uint32_t shift = threadIdx.x & 31u & ~(uint32_t)(kTeam - 1), below = (1u << sub) - 1u;
+  uint32_t *list = lists[team];
+  const uint32_t first = xcd_block(blockIdx.x, gridDim.x) * (uint32_t)kTeamRows;
+  const uint32_t i = first + (uint32_t)team;
+  const bool active = i < nf;
+  const double4 a0 = rec_at(rec0, active ? i : 0u), a1 = rec_at(rec1, active ? i : 0u);
+  PairSums S;
+  sums_zero(S);
+  const double rho = KEEP ? P.two_h + P.skin_max : P.two_h;
+  const double rho2 = KEEP ? rho * rho : P.two_h2;
+  int cnt = 0, done = 0, kept = 0, tested = 0;  // neighbours listed and summed, candidates kept and tested
+  auto ranks = [&](bool in, int &n) {  // lanes of the team below this one that have one; n: of the team
+    const unsigned long long m = __ballot(in);
+    const uint32_t t = ((upper ? (uint32_t)(m >> 32) : (uint32_t)m) >> shift) & ((1u << kTeam) - 1u);
+    n = __popc(t);
+    return __popc(t & below);
+  };
+  // candidates 0 .. n - 1 of the team (at most nmax in the wave): record index(k)
+  auto test = [&](int n, int nmax, auto index) {
+    for (int t = 0; t < nmax; t += kPer * kTeam) {
+      uint32_t j[kPer];
+      double4 b[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int k = t + u * kTeam + sub;
+        j[u] = index(k, k < n);
+        if (u < 2 || t + u * kTeam < nmax) b[u] = rec_at(rec0, j[u]);
+      }
+      wave_lds_sync();  // the entries are read before neighbours take their places
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (u > 0 && t + u * kTeam >= nmax) break;
+        const double r2 = dist2_exact<DIM>(b[u].x - a0.x, b[u].y - a0.y, DIM == 3 ? b[u].z - a0.z : 0.0);
+        const bool other = t + u * kTeam + sub < n && j[u] != i, in = other && r2 <= P.two_h2;
+        int m;
+        const int at = ranks(in, m);
+        list[in ? cnt + at : kList] = j[u];
+        cnt += m;
+        if (KEEP) {
+          const bool keep = other && r2 <= rho2;
+          const int k = kept + ranks(keep, m);
+          kept += m;
+          if (keep && k < kKeepChunks * kPairList)
+            kl.ent[kept_entry(i, k / kPairList, k % kPairList)] = j[u] | (in ? 0u : kSkinTag);
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+    }
+    tested += n;
+  };
+  // the pair body over the list where another chunk might not fit, or at the end
+  auto run_list = [&](bool end) {
+    const int cmax = team_max(cnt);
+    if (!end && cmax <= kList - kChunk) return;
+    wave_lds_sync();
+    for (int t = (sub - done) & (kTeam - 1), t0 = 0; t0 < cmax; t0 += kTeam, t += kTeam) {
+      if (t < cnt) {
+        const uint32_t j = list[t];
+        pair_body_f64<DIM, PST4>(P, a0, a1, rec_at(rec0, j), rec_at(rec1, j), S);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    done += cnt;
+    cnt = 0;
+    wave_lds_sync();
+  };
+  if (KEPT) {
+    const unsigned long long book = active ? kl.cnt[i] : 0ull;
+    const int nch = (int)(book >> kKeptNchShift);
+    const int n = nch ? (nch - 1) * kPairList + kept_count(book, nch - 1) : 0;
+    test(n, team_max(n), [&](int k, bool in) {
+      return in ? kl.ent[kept_entry(i, k / kPairList, k % kPairList)] & ~kSkinTag : 0u;
+    });
+  } else {
+    const CellPos cp = cellpos_of<DIM>(g, a0.x, a0.y, a0.z);
+    const float rr = (float)rho * (float)g.invR;
+    const float rr2 = rr * rr * (1.0f + 4.0f * kWalkSlack);
+    const int nrows = DIM == 3 ? (2 * g.reach + 1) * (2 * g.reach + 1) : 2 * g.reach + 1;
+    for (int r0 = 0; r0 < nrows; r0 += kTeam) {
+      uint32_t fb = 0, fl = 0, db = 0, dl = 0;  // this lane's row
+      if (active && r0 + sub < nrows) row_windows<DIM>(g, cp, rr2, r0 + sub, cs_f, cs_d, nf, fb, fl, db, dl);
+      __builtin_amdgcn_wave_barrier();
+      const bool walls = __ballot(dl > 0u) != 0ull;
+      if (LONG) {
+        auto row = [&](int q, uint32_t rb, uint32_t rl) {
+          const uint32_t lo = __shfl(rb, q, kTeam);
+          const int len = (int)__shfl(rl, q, kTeam), lmax = team_max(len);
+          for (int base = 0; base < lmax; base += kChunk) {
+            run_list(false);
+            const uint32_t from = lo + (uint32_t)base;
+            test(min(max(len - base, 0), kChunk), min(lmax - base, kChunk),
+                 [&](int k, bool in) { return in ? from + (uint32_t)k : 0u; });
+          }
+        };
+        for (int q = 0; q < kTeam && r0 + q < nrows; ++q) {
+          row(q, fb, fl);
+          if (walls) row(q, db, dl);
+        }
+      } else {
+        const int len = (int)(fl + dl), pre = team_scan(len, sub) - len;
+        const int total = __shfl(pre + len, kTeam - 1, kTeam), all = team_max(total);
+        for (int base = 0; base < all; base += kChunk) {
+          run_list(false);
+          // entries [e0, e0 + n) of the set are records b, b + 1, ...
+          const int from = cnt;
+          auto expand = [&](int e0, int n, uint32_t b) {
+            const int e1 = min(e0 + n, base + kChunk);
+            int e = max(e0, base);
+            b += (uint32_t)(e - e0);
+            while (__ballot(e < e1)) {
+              list[e < e1 ? from + e - base : kList] = b;
+              ++e;
+              ++b;
+            }
+          };
+          expand(pre, (int)fl, fb);
+          if (walls) expand(pre + (int)fl, (int)dl, db);
+          wave_lds_sync();
+          test(min(max(total - base, 0), kChunk), min(all - base, kChunk), [&](int k, bool in) {
+            const uint32_t j = list[in ? from + k : kList];
+            return in ? j : 0u;
+          });
+        }
+      }
+    }
+  }
+  run_list(true);
+  if (KEEP && sub == 0 && active) {
+    unsigned long long book = 0ull;
+    const int nch = min((kept + kPairList - 1) / kPairList, kKeepChunks);
+    for (int c = 0; c < nch; ++c) book |= (unsigned long long)min(kept - c * kPairList, kPairList) << (6 * c);
+    kl.cnt[i] = book | ((unsigned long long)nch << kKeptNchShift);
+    if (kept > kKeepChunks * kPairList) sc->vovf = 1u;
+  }
+  __builtin_amdgcn_wave_barrier();
+  int same;
+  ranks(S.coincident, same);
+  double v[NS];
+  each_sum<DIM>(S, [&](double &x, int q) { v[q] = x; });
+  team_reduce<kTeam / 2, NS>(v, sub);
+#pragma unroll
+  for (int k = 0; k < team_left<kTeam / 2, NS>(); ++k) sums[team_slot<kTeam / 2, NS>(sub, k)][team] = v[k];
+  if (sub == 0) {
+    counts[0][team] = (uint32_t)done;
+    counts[1][team] = (uint32_t)tested;
+    counts[2][team] = (uint32_t)same;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int row = (int)threadIdx.x & (kTeamRows - 1);
+  PairSums T;
+  sums_zero(T);
+  each_sum<DIM>(T, [&](double &x, int q) { x = sums[q][row]; });
+  T.nnb = counts[0][row];
+  T.ntest = counts[1][row];
+  T.coincident = counts[2][row] != 0u;
+  const uint32_t mine = first + threadIdx.x;
+  pair_epilogue<DIM>(P, sc, out, cand, mine, threadIdx.x < kTeamRows && mine < nf, T);
+}
+
+// Whether the pass runs by teams: up to the count where one lane per particle
+// (k_pair_f64, k_pair_kept_f64) catches up.  With a lane each, a wave's chain
+// of loads takes 240 us in 3D (36 us in 2D) whatever the count, and the waves
+// come in rounds of 4,096; with a lane each the instructions per particle are
+// fewer.  Measured, us, lane / team: 3D search, cells of h 251 / 35 (17,500
+// particles), 769 / 567 (651,000), 2,240 / 1,543 (1.76M), 4,445 / 4,510 (5.2M);
+// cells of 2h 263 / 41, 865 / 637, 2,112 / 1,743, 5,276 / 5,169; building lists
+// 293 / 45, 978 / 818, 2,056 / 2,244; from kept lists 64 / 23, 83 / 55 (70,400),
+// 113 / 124 (193,000).  2D search 37 / 12 (5,000), 41 / 28 (80,000), 46 / 46
+// (155,000); from kept lists 16 / 11 (20,000), 20 / 25 (80,000).  The plain
+// search and the one that builds lists change over at the same count, so that
+// their sums are the same bit for bit.
+template <int DIM>
+static bool by_team(uint32_t nf, int64_t nrec, int mode) {
+  if (nrec > (int64_t)1 << 27) return false;  // rec_at's offsets
+  if (mode == kPairKept) return nf <= (DIM == 3 ? 130000u : 40000u);  // within the next line: lists of this kernel
+  return nf <= (DIM == 3 ? 2000000u : 120000u);
+}
+
 template <int DIM>
 void launch_pair_f64_inst(const Phys &P, const Grid &g, const double4 *rec0, const double4 *rec1,
-                          const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, Scalars *sc, const Rates &out,
-                          uint32_t *cand, const KeptLists &kl, int mode, hipStream_t s) {
+                          const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, int64_t nrec, Scalars *sc,
+                          const Rates &out, uint32_t *cand, const KeptLists &kl, int mode, hipStream_t s) {
   dim3 gr(grid_for(nf)), bl(kBlock);
   const bool p4 = P.pst_n == 4.0;
-  if (mode == kPairSearch) {
+  if (by_team<DIM>(nf, nrec, mode)) {
+    const bool lng = DIM == 3 && g.reach == 1;
+    gr = dim3(grid_for(nf, kTeamRows));
+#define WB_TEAM(MODE, LONG)                                                                                       \
+  do {                                                                                                            \
+    if (p4)                                                                                                       \
+      hipLaunchKernelGGL((k_pair_team_f64<DIM, true, MODE, LONG>), gr, bl, 0, s, P, g, rec0, rec1, cs_f, cs_d,    \
+                         nf, sc, out, cand, kl);                                                                  \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_pair_team_f64<DIM, false, MODE, LONG>), gr, bl, 0, s, P, g, rec0, rec1, cs_f, cs_d,   \
+                         nf, sc, out, cand, kl);                                                                  \
+  } while (0)
+    if (mode == kPairKept) WB_TEAM(kPairKept, false);
+    else if (mode == kPairSearchKeep && lng) WB_TEAM(kPairSearchKeep, DIM == 3);
+    else if (mode == kPairSearchKeep) WB_TEAM(kPairSearchKeep, false);
+    else if (lng) WB_TEAM(kPairSearch, DIM == 3);
+    else WB_TEAM(kPairSearch, false);
+#undef WB_TEAM
+  } else if (mode == kPairSearch) {
     if (p4)
       hipLaunchKernelGGL((k_pair_f64<DIM, true, false>), gr, bl, 0, s, P, g, rec0, rec1, cs_f, cs_d, nf, sc, out, cand,
                          kl);
@@ -366,15 +684,15 @@ void launch_pair_f64_inst(const Phys &P, const Grid &g, const double4 *rec0, con
 }
 
 hipError_t launch_pair_f64(const Phys &P, const Grid &g, const double4 *rec0, const double4 *rec1,
-                           const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, Scalars *sc, const Rates &out,
-                           uint32_t *cand, int mode, uint32_t *kent, unsigned long long *kcnt, hipStream_t s) {
+                           const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, int64_t nrec, Scalars *sc,
+                           const Rates &out, uint32_t *cand, int mode, uint32_t *kent, unsigned long long *kcnt, hipStream_t s) {
   if (nf == 0) return hipSuccess;
   if (mode != kPairSearch && (!kent || !kcnt)) return hipErrorInvalidValue;
   KeptLists kl{kent, kcnt};
   if (P.dim == 2)
-    launch_pair_f64_inst<2>(P, g, rec0, rec1, cs_f, cs_d, nf, sc, out, cand, kl, mode, s);
+    launch_pair_f64_inst<2>(P, g, rec0, rec1, cs_f, cs_d, nf, nrec, sc, out, cand, kl, mode, s);
   else
-    launch_pair_f64_inst<3>(P, g, rec0, rec1, cs_f, cs_d, nf, sc, out, cand, kl, mode, s);
+    launch_pair_f64_inst<3>(P, g, rec0, rec1, cs_f, cs_d, nf, nrec, sc, out, cand, kl, mode, s);
   return hipGetLastError();
 }
 
