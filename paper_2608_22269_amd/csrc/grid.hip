@@ -104,8 +104,10 @@ constexpr int64_t kFusedTiles = 4096;
 // Particles up to which the hash also adds up the tiles: few tiles hold them
 // all, and beyond, the atomics on those wait for one another longer than a
 // pass over the counts takes (660,000 particles: hash 57 us with them, 10 us
-// and a pass of 4 us without; at 5,000 they cost nothing and save a launch).
-constexpr int64_t kTileAtomics = 32768;
+// and a pass of 4 us without; 27,000 in raster order 21 us with, 4.6 and 2.9
+// without; a step of 17,500 189 us with, 185 without; of 10,153 in 2D 82 with,
+// 85 without; of 1,250 86 with, 90 without).
+constexpr int64_t kTileAtomics = 12000;
 
 template <bool CLEAR, bool SUMMED>
 __global__ void __launch_bounds__(256) k_scan_apply(uint32_t *in, uint32_t *out, const uint32_t *__restrict__ sums,

@@ -1,5 +1,5 @@
 """The sort at the edges of its dispatch: the particle count up to which the
-hash adds up the scan's tiles (32,768), the key count up to which the scan
+hash adds up the scan's tiles (12,000), the key count up to which the scan
 works from plain tile sums (4,096 tiles of 1,024 keys), and particles given in
 an order that has nothing to do with space (the places inside the cells come
 from the original indices).  Against the oracle at the parity bars."""
@@ -19,7 +19,7 @@ def _shuffled(case, seed):
     return dict(case, **{k: case[k][order] for k in ("x", "u", "phi", "kind", "normal")})
 
 
-@pytest.mark.parametrize("n,hi", [(32768, 1.0), (32769, 1.0), (500, 1.0), (500, 8.15), (500, 8.37)])
+@pytest.mark.parametrize("n,hi", [(12000, 1.0), (12001, 1.0), (32769, 1.0), (500, 1.0), (500, 8.15), (500, 8.37)])
 def test_sort_dispatch(n, hi):
     """hi: extent of the domain; at dx = 0.02 (cells of 0.052) 1 m makes 12
     tiles of sort keys, 8.15 m 157 x 160 x 160 keys (3,925 tiles) and 8.37 m
