@@ -99,80 +99,96 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const float *__restrict__ w, co
   if (on && lane == 0) s[b] = p + w[kOffB3];
 }
 
-// tanh form of GELU and its derivative from one tanh.
+// tanh form of GELU and its derivative, (1 + tanh u) / 2 as 1 / (1 + exp(-2u)).
 __device__ __forceinline__ void gelu_both(float z, float &a, float &d) {
   const float c = 0.7978845608028654f;
-  const float th = tanhf(c * (z + 0.044715f * z * z * z));
-  a = 0.5f * z * (1.0f + th);
-  d = 0.5f * (1.0f + th) + 0.5f * z * (1.0f - th * th) * c * (1.0f + 3.0f * 0.044715f * z * z);
+  const float s = 1.0f / (1.0f + expf(-2.0f * c * (z + 0.044715f * z * z * z)));  // (1 + tanh) / 2
+  a = z * s;
+  d = s + 2.0f * z * (s * (1.0f - s)) * c * (1.0f + 3.0f * 0.044715f * z * z);
 }
 
 // Loss and parameter gradients of a batch, summed over the rows of a block:
 // part[block][0 .. kMlpParams) and the block's loss at [kMlpParams].
 //
 // One wave per row, lane = hidden unit, rpw rows per wave.  A lane keeps its
-// column and its row of W2 and its column of W1 in registers (144 values) and
-// the gradients of its columns of W1 and W2 (80 sums), so a row costs 224 FMAs
-// per lane and a few LDS broadcasts, and the activations never reach memory.
-// The four waves' sums are added in wave order, the blocks' in block order by
-// k_mlp_reduce: the result depends only on the rows' order.  It replaces one
-// kernel each for forward, loss and rows' backward pass and one thread per
-// parameter that walked the whole batch: an epoch of 65,536 rows in batches
-// of 4,096 took 31.9 ms, 97% of it in that walk, and takes 0.47 ms (19 us a
-// batch here and 7 us in the reduction).
+// columns of W1 and W2 in registers (80 values) and the gradients of those (80
+// sums), so a row costs 224 FMAs per lane and a few LDS broadcasts, and the
+// activations never reach memory.  Bound by a row's chain of instructions (2.9
+// us with one wave per SIMD): the rows of W2 come from LDS, which leaves room
+// for two waves per SIMD, dot products run in four sums, and GELU's tanh is
+// one exponential.  The sums of waves u and u + 4 are added, then the four in
+// order, the blocks' in block order by k_mlp_reduce: the result depends only
+// on the rows' order.  A batch of 4,096 rows: 19.3 us with one wave per SIMD,
+// 13.8 so, and 4.2 in the reduction; an epoch of 65,536 rows in such batches
+// 0.32 ms (31.9 ms with one kernel each for forward, loss and the rows'
+// backward pass and one thread per parameter that walked the whole batch).
 constexpr int kPart = kMlpParams + 1;
+constexpr int kGradWaves = 8;
 
-__global__ void __launch_bounds__(256, 1) k_mlp_grad(const float *__restrict__ w, const float *__restrict__ mean,
+// c + a . b in four sums (one is a chain of N dependent FMAs).
+template <int N>
+__device__ __forceinline__ float dot(float c, const float *a, const float *b) {
+  float s[4] = {c, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int k = 0; k < N; ++k) s[k & 3] += a[k] * b[k];
+  return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+__global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(const float *__restrict__ w, const float *__restrict__ mean,
                                                      const float *__restrict__ std, const float *__restrict__ X,
                                                      const float *__restrict__ y, const float *__restrict__ wt,
                                                      const int32_t *__restrict__ perm, int64_t off, int64_t B, int rpw,
                                                      float *__restrict__ part) {
-  __shared__ __align__(16) float sx[4][kMlpIn], sa[4][kMlpHid], sd[4][kMlpHid];
-  __shared__ float sum[kPart];
+  __shared__ __align__(16) float sx[kGradWaves][kMlpIn], sa[kGradWaves][kMlpHid], sd[kGradWaves][kMlpHid];
+  __shared__ __align__(16) float w2l[kMlpHid][kMlpHid + 4];  // rows of W2 (a stride of 68: 16 lanes on all banks)
+  __shared__ float sum[kGradWaves / 2][kPart];
   const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
-  float w1[kMlpIn], w2c[kMlpHid], w2r[kMlpHid];
+  float w1[kMlpIn], w2c[kMlpHid];
 #pragma unroll
   for (int i = 0; i < kMlpIn; ++i) w1[i] = w[kOffW1 + i * kMlpHid + lane];
 #pragma unroll
   for (int k = 0; k < kMlpHid; ++k) w2c[k] = w[kOffW2 + k * kMlpHid + lane];
-  static_assert(kOffW2 % 4 == 0, "rows of W2 are read four values at a time (the trainer's weights are 256-byte aligned)");
-#pragma unroll
-  for (int k = 0; k < kMlpHid; k += 4) {
-    const float4 q = *reinterpret_cast<const float4 *>(w + kOffW2 + lane * kMlpHid + k);
-    w2r[k] = q.x;
-    w2r[k + 1] = q.y;
-    w2r[k + 2] = q.z;
-    w2r[k + 3] = q.w;
-  }
+  for (int p = threadIdx.x; p < kMlpHid * kMlpHid; p += 64 * kGradWaves) w2l[p / kMlpHid][p % kMlpHid] = w[kOffW2 + p];
   const float b1 = w[kOffB1 + lane], b2 = w[kOffB2 + lane], w3 = w[kOffW3 + lane], b3 = w[kOffB3];
   float g1[kMlpIn], g2[kMlpHid], gb1 = 0.0f, gb2 = 0.0f, g3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
 #pragma unroll
   for (int i = 0; i < kMlpIn; ++i) g1[i] = 0.0f;
 #pragma unroll
   for (int k = 0; k < kMlpHid; ++k) g2[k] = 0.0f;
-  const int64_t b0 = ((int64_t)blockIdx.x * 4 + v) * rpw;
+  const int64_t b0 = ((int64_t)blockIdx.x * kGradWaves + v) * rpw;
   const int64_t b_end = b0 + rpw < B ? b0 + rpw : B;
+  // the next row's inputs are requested before this one is worked on, and the
+  // index of the one after
+  const float mu = lane < kMlpIn ? mean[lane] : 0.0f, sg = lane < kMlpIn ? std[lane] : 1.0f;
+  auto row_of = [&](int64_t b) { return b >= b_end ? (int64_t)-1 : perm ? (int64_t)perm[off + b] : off + b; };
+  float xn = 0.0f, yn = 0.0f, wn = 1.0f;
+  auto request = [&](int64_t row) {
+    if (row < 0) return;
+    if (lane < kMlpIn) xn = X[row * kMlpIn + lane];
+    yn = y[row];
+    if (wt) wn = wt[row];
+  };
+  request(row_of(b0));
+  int64_t ahead = row_of(b0 + 1);
+  __syncthreads();
   for (int64_t b = b0; b < b_end; ++b) {
-    const int64_t row = perm ? (int64_t)perm[off + b] : off + b;
-    if (lane < kMlpIn) sx[v][lane] = (X[row * kMlpIn + lane] - mean[lane]) / std[lane];
+    const float yv = yn, wv = wn;
+    if (lane < kMlpIn) sx[v][lane] = (xn - mu) / sg;
+    request(ahead);
+    ahead = row_of(b + 2);
     wave_lds_order();
-    float z = b1;
-#pragma unroll
-    for (int i = 0; i < kMlpIn; ++i) z += sx[v][i] * w1[i];
+    float z = dot<kMlpIn>(b1, sx[v], w1);
     float a1, d1, a2, d2;
     gelu_both(z, a1, d1);
     sa[v][lane] = a1;
     wave_lds_order();
-    float q = b2;
-#pragma unroll
-    for (int k = 0; k < kMlpHid; ++k) q += sa[v][k] * w2c[k];
+    const float q = dot<kMlpHid>(b2, sa[v], w2c);
     gelu_both(q, a2, d2);
     float s = a2 * w3;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     s += b3;
     // dL/ds of the weighted mean BCE and the row's loss
-    const float yv = y[row], wv = wt ? wt[row] : 1.0f;
     const float sig = 1.0f / (1.0f + expf(-s));
     const float ds = wv * (sig - yv) / (float)B;
     loss += wv * (fmaxf(s, 0.0f) - s * yv + log1pf(expf(-fabsf(s))));
@@ -180,10 +196,7 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const float *__restrict__ w
     const float e2 = ds * w3 * d2;
     sd[v][lane] = e2;
     wave_lds_order();
-    float t = 0.0f;
-#pragma unroll
-    for (int k = 0; k < kMlpHid; ++k) t += sd[v][k] * w2r[k];
-    const float e1 = t * d1;
+    const float e1 = dot<kMlpHid>(0.0f, sd[v], w2l[lane]) * d1;
 #pragma unroll
     for (int i = 0; i < kMlpIn; ++i) g1[i] += sx[v][i] * e1;
 #pragma unroll
@@ -194,9 +207,11 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const float *__restrict__ w
     gb3 += ds;
     wave_lds_order();  // the row's LDS is rewritten for the next one
   }
-  for (int u = 0; u < 4; ++u) {
-    if (v == u) {
-      auto put = [&](int p, float x) { sum[p] = u == 0 ? x : sum[p] + x; };
+  // wave u's and wave u + 4's sums, then the four of them in order
+  for (int u = 0; u < 2; ++u) {
+    if (v / (kGradWaves / 2) == u) {
+      float *dst = sum[v % (kGradWaves / 2)];
+      auto put = [&](int p, float x) { dst[p] = u == 0 ? x : dst[p] + x; };
 #pragma unroll
       for (int i = 0; i < kMlpIn; ++i) put(kOffW1 + i * kMlpHid + lane, g1[i]);
       put(kOffB1 + lane, gb1);
@@ -211,14 +226,20 @@ __global__ void __launch_bounds__(256, 1) k_mlp_grad(const float *__restrict__ w
     }
     __syncthreads();
   }
-  for (int p = threadIdx.x; p < kPart; p += 256) part[(size_t)blockIdx.x * kPart + p] = sum[p];
+  for (int p = threadIdx.x; p < kPart; p += 64 * kGradWaves) {
+    float t = sum[0][p];
+#pragma unroll
+    for (int u = 1; u < kGradWaves / 2; ++u) t += sum[u][p];
+    part[(size_t)blockIdx.x * kPart + p] = t;
+  }
 }
 
 // Sums the blocks' partial gradients (and the losses: *loss the batch mean,
 // acc += or = it) and, with adam, updates the parameters.  kRedParams
 // parameters per block, each summed by kRedSlices threads over a contiguous
-// share of the blocks: one thread per parameter waited out a serial chain of
-// loads on 21 of 256 CUs.
+// share of the blocks, eight loads in flight (6.8 us one at a time, 4.2 so,
+// 4,096 rows): one thread per parameter waited out a serial chain of loads on
+// 21 of 256 CUs.
 constexpr int kRedParams = 64, kRedSlices = 16;
 
 struct AdamArgs {
@@ -244,7 +265,13 @@ __global__ void __launch_bounds__(kRedParams *kRedSlices)
   const int k0 = sl * per, k1 = k0 + per < nblk ? k0 + per : nblk;
   float t = 0.0f;
   if (p < kPart)
-    for (int k = k0; k < k1; ++k) t += part[(size_t)k * kPart + p];
+    for (int k = k0; k < k1; k += 8) {  // eight loads in flight, added in block order
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = part[(size_t)min(k + u, k1 - 1) * kPart + p];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += k + u < k1 ? x[u] : 0.0f;
+    }
   sh[sl][c] = t;
   __syncthreads();
   if (sl != 0 || p >= kPart) return;
@@ -472,13 +499,14 @@ struct sph_mlp {
 namespace {
 
 // Rows per wave and blocks of the gradient kernel for a batch: one wave per
-// row up to 1,024 rows (the chip's SIMDs), then more rows per wave, so that
+// row up to 2,048 rows (two waves per SIMD), then more rows per wave, so that
 // there are at most kGradBlocks block sums (21 KB each).
 constexpr int64_t kGradBlocks = 256;
 
 void grad_split(int64_t B, int &rpw, int &nblk) {
-  rpw = (int)((B + 4 * kGradBlocks - 1) / (4 * kGradBlocks));
-  nblk = (int)((B + 4 * (int64_t)rpw - 1) / (4 * (int64_t)rpw));
+  constexpr int64_t waves = kGradWaves * kGradBlocks;
+  rpw = (int)((B + waves - 1) / waves);
+  nblk = (int)((B + kGradWaves * (int64_t)rpw - 1) / (kGradWaves * (int64_t)rpw));
 }
 
 size_t mlp_carve(sph_mlp *m, uintptr_t base, int64_t B) {
@@ -499,7 +527,7 @@ size_t mlp_carve(sph_mlp *m, uintptr_t base, int64_t B) {
   m->z1 = take(B * kMlpHid);
   m->z2 = take(B * kMlpHid);
   m->a2 = take(B * kMlpHid);
-  m->part = take(std::min<int64_t>(kGradBlocks, (B + 3) / 4) * kPart);  // any batch up to B
+  m->part = take(std::min<int64_t>(kGradBlocks, (B + kGradWaves - 1) / kGradWaves) * kPart);  // any batch up to B
   m->loss = take(1);
   m->loss_acc = take(1);
   return off + 256;
@@ -512,7 +540,7 @@ hipError_t mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const float
                          int64_t B, float *acc, int acc_reset, const AdamArgs *adam) {
   int rpw, nblk;
   grad_split(B, rpw, nblk);
-  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(256), 0, m->s, m->w, m->mean, m->std, X, y, w, perm, off,
+  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(64 * kGradWaves), 0, m->s, m->w, m->mean, m->std, X, y, w, perm, off,
                      B, rpw, m->part);
   hipLaunchKernelGGL(k_mlp_reduce, dim3((kPart + kRedParams - 1) / kRedParams), dim3(kRedParams * kRedSlices), 0, m->s,
                      m->part, nblk, B, m->g, m->loss, acc, acc_reset, adam ? 1 : 0, adam ? *adam : AdamArgs{});

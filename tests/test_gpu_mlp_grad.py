@@ -16,7 +16,7 @@ from test_gpu_mlp import _data
 pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore::RuntimeWarning")]
 
 
-@pytest.mark.parametrize("B,max_batch", [(1, 1), (3, 7), (4, 4), (5, 1025), (1023, 1023), (1024, 1025), (1025, 1025),
+@pytest.mark.parametrize("B,max_batch", [(1, 1), (3, 7), (4, 4), (5, 1025), (8, 8), (9, 16), (1023, 1023), (1025, 1025), (2048, 2048),
                                          (2049, 4100), (4100, 4100)])
 def test_gradient_row_split(B, max_batch):
     from paper_2608_22269_amd import learn
