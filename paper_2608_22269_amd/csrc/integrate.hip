@@ -95,6 +95,7 @@ __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, 
   double u2 = 0.0;
   if (i < n) {
     const double dt = sc->dt;
+    const double m = rec0 ? f.m[i] : 0.0;  // every load before the first store
     double xn[3] = {0.0, 0.0, 0.0}, un[3] = {0.0, 0.0, 0.0}, pn;
     if (stage == 1) {  // the state of t^n is in the stage-0 arrays (the caller swapped them)
       pn = f.phi0[i] + dt * r.dphi[i];
@@ -126,7 +127,7 @@ __global__ void __launch_bounds__(256) k_stage_f64(Phys P, FluidF64 f, Rates r, 
       if (!ok) atomicOr(&sc->err, kErrNonFinite);
     }
     if (rec0) {
-      const double V = f.m[i] / (P.rho0 * exp(pn * P.inv_c02));
+      const double V = m / (P.rho0 * exp(pn * P.inv_c02));
       rec0[i] = make_double4(xn[0], xn[1], xn[2], pn);
       rec1[i] = make_double4(un[0], un[1], un[2], V);
     }
@@ -349,21 +350,33 @@ __global__ void k_gather_dummies(SortScratch ss, const uint32_t *__restrict__ st
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nd) return;
   const uint2 from = perm[t];
-  const uint32_t o = from.x, k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
-  for (int a = 0; a < dim; ++a) {
-    dst.x[a][k] = src.x[a][o];
-    dst.n[a][k] = src.n[a][o];
+  const uint32_t o = from.x;
+  // every load before the first store, as in the fluid's reorder
+  double x[3] = {0.0, 0.0, 0.0}, nr[3] = {0.0, 0.0, 0.0}, x0[3] = {0.0, 0.0, 0.0}, n0[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (a == dim) break;
+    x[a] = src.x[a][o];
+    nr[a] = src.n[a][o];
+    if (src.mov) x0[a] = src.x0[a][o];
+    if (src.n0[0]) n0[a] = src.n0[a][o];
   }
-  dst.m[k] = src.m[o];
-  dst.phi_in[k] = src.phi_in[o];
+  const double m = src.m[o], phi = src.phi_in[o];
+  const uint8_t mov = src.mov ? src.mov[o] : 0;
+  const uint32_t k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (a == dim) break;
+    dst.x[a][k] = x[a];
+    dst.n[a][k] = nr[a];
+    if (src.mov) dst.x0[a][k] = x0[a];
+    if (src.n0[0]) dst.n0[a][k] = n0[a];
+  }
+  dst.m[k] = m;
+  dst.phi_in[k] = phi;
   dst.id[k] = from.y;
   dst.src[k] = -1;
-  if (src.mov) {
-    dst.mov[k] = src.mov[o];
-    for (int a = 0; a < dim; ++a) dst.x0[a][k] = src.x0[a][o];
-  }
-  if (src.n0[0])
-    for (int a = 0; a < dim; ++a) dst.n0[a][k] = src.n0[a][o];
+  if (src.mov) dst.mov[k] = mov;
 }
 
 hipError_t launch_gather_dummies(const SortScratch &ss, const uint32_t *start, const uint2 *perm, int64_t nd,

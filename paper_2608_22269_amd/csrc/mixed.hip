@@ -118,28 +118,40 @@ __global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, SortScrat
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const uint2 from = perm[t];
-  const uint32_t o = from.x, k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
-  uint32_t c = src.cell[o];
-  dst.cell[k] = c;
-  float of[3] = {0.f, 0.f, 0.f}, uf[3] = {0.f, 0.f, 0.f};
+  const uint32_t o = from.x;
+  // every load before the first store, as in the FP64 reorder
+  const uint32_t c = src.cell[o];
+  float of[3] = {0.f, 0.f, 0.f}, uf[3] = {0.f, 0.f, 0.f}, oc[DIM], uc[DIM], dx1[DIM], du1[DIM];
+  double dphi1 = 0.0;
+#pragma unroll
   for (int a = 0; a < DIM; ++a) {
     of[a] = src.o[a][o];
     uf[a] = src.u[a][o];
+    oc[a] = src.oc[a][o];
+    uc[a] = src.uc[a][o];
+    dx1[a] = with_stage0 ? src.dx1[a][o] : 0.f;
+    du1[a] = with_stage0 ? src.du1[a][o] : 0.f;
+  }
+  const double ph = src.phi[o];
+  const float m = src.m[o];
+  if (with_stage0) dphi1 = src.dphi1[o];
+  const uint32_t k = sorted_place(ss.key, start, perm, (uint32_t)t, from);
+  dst.cell[k] = c;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) {
     dst.o[a][k] = of[a];
-    dst.oc[a][k] = src.oc[a][o];
+    dst.oc[a][k] = oc[a];
     dst.u[a][k] = uf[a];
-    dst.uc[a][k] = src.uc[a][o];
+    dst.uc[a][k] = uc[a];
     if (with_stage0) {
-      dst.dx1[a][k] = src.dx1[a][o];
-      dst.du1[a][k] = src.du1[a][o];
+      dst.dx1[a][k] = dx1[a];
+      dst.du1[a][k] = du1[a];
     }
   }
-  double ph = src.phi[o];
   dst.phi[k] = ph;
-  float m = src.m[o];
   dst.m[k] = m;
   dst.id[k] = from.y;
-  if (with_stage0) dst.dphi1[k] = src.dphi1[o];
+  if (with_stage0) dst.dphi1[k] = dphi1;
   float V = (float)((double)m / (P.rho0 * exp(ph * P.inv_c02)));
   int cc[3] = {cell_x(c), cell_y(c), cell_z(c)};
   float xa[3] = {0.f, 0.f, 0.f};
@@ -945,19 +957,38 @@ __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed 
     uint32_t bad = 0u;
     int cc[3] = {cell_x(c), cell_y(c), cell_z(c)};
     float of[3] = {0.f, 0.f, 0.f}, uf[3] = {0.f, 0.f, 0.f};
+    // every load before the first store (the compiler must take the arrays
+    // for one another's, and waited for each axis in turn)
+    float o_[DIM], oc_[DIM], u_[DIM], uc_[DIM], dx1[DIM], du1[DIM];
+    double dus[DIM], acc[DIM];
+#pragma unroll
     for (int a = 0; a < DIM; ++a) {
-      float o = f.o[a][i], oc = f.oc[a][i], u = f.u[a][i], uc = f.uc[a][i];
+      o_[a] = f.o[a][i];
+      oc_[a] = f.oc[a][i];
+      u_[a] = f.u[a][i];
+      uc_[a] = f.uc[a][i];
+      dus[a] = r.dus[a][i];
+      acc[a] = r.acc[a][i];
+      dx1[a] = stage == 1 ? 0.f : f.dx1[a][i];
+      du1[a] = stage == 1 ? 0.f : f.du1[a][i];
+    }
+    const double dphi = r.dphi[i], dphi1 = stage == 1 ? 0.0 : f.dphi1[i];
+    double ph = f.phi[i];
+    const float m = write_rec ? f.m[i] : 0.f;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+      float o = o_[a], oc = oc_[a], u = u_[a], uc = uc_[a];
       // position first (uses the stage's velocity), then velocity
-      const double vx = ((double)u - (double)uc + r.dus[a][i]) * dt;
-      const double va = r.acc[a][i] * dt;
+      const double vx = ((double)u - (double)uc + dus[a]) * dt;
+      const double va = acc[a] * dt;
       if (stage == 1) {
         kahan_add(o, oc, vx);
         kahan_add(u, uc, va);
         f.dx1[a][i] = (float)vx;
         f.du1[a][i] = (float)va;
       } else {
-        kahan_add(o, oc, 0.5 * (vx - (double)f.dx1[a][i]));
-        kahan_add(u, uc, 0.5 * (va - (double)f.du1[a][i]));
+        kahan_add(o, oc, 0.5 * (vx - (double)dx1[a]));
+        kahan_add(u, uc, 0.5 * (va - (double)du1[a]));
       }
       // keep the offset inside its cell: move whole cells, subtract k R exactly
       const double ov = (double)o - (double)oc;
@@ -972,6 +1003,7 @@ __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed 
       f.oc[a][i] = oc;
       f.u[a][i] = u;
       f.uc[a][i] = uc;
+      oc_[a] = oc;
       of[a] = o;
       uf[a] = u;
       u2 += (double)u * (double)u;
@@ -979,25 +1011,24 @@ __global__ void __launch_bounds__(256) k_stage_mixed(Phys P, Grid g, FluidMixed 
     // a particle whose cell left the grid is an error (reported at the next
     // synchronisation); the packed fields are kept from wrapping meanwhile
     for (int a = 0; a < DIM; ++a) {
-      const double xa = g.lo[a] + (double)cc[a] * g.R + ((double)of[a] - (double)f.oc[a][i]);
+      const double xa = g.lo[a] + (double)cc[a] * g.R + ((double)of[a] - (double)oc_[a]);
       if (cc[a] < 0 || cc[a] >= g.N[a] || !(xa >= g.lo[a] && xa <= g.hi[a])) bad |= kErrDomain;
     }
     for (int a = 0; a < 3; ++a) cc[a] = min(max(cc[a], 0), a == 2 ? 1023 : 2047);
     c = pack_cell(cc[0], cc[1], cc[2]);
     f.cell[i] = c;
-    const double dp = r.dphi[i] * dt;
-    double ph = f.phi[i];
+    const double dp = dphi * dt;
     if (stage == 1) {
       ph += dp;
       f.dphi1[i] = dp;
     } else {
-      ph += 0.5 * (dp - f.dphi1[i]);
+      ph += 0.5 * (dp - dphi1);
     }
     f.phi[i] = ph;
     if (!isfinite(ph)) bad |= kErrNonFinite;
     if (bad) atomicOr(&sc->err, bad);
     if (write_rec) {  // the records of the new state, as the reorder writes them
-      const float V = (float)((double)f.m[i] / (P.rho0 * exp(ph * P.inv_c02)));
+      const float V = (float)((double)m / (P.rho0 * exp(ph * P.inv_c02)));
       float xa[3] = {0.f, 0.f, 0.f};
       for (int a = 0; a < DIM; ++a) xa[a] = (float)pos_of(g.lo[a], g.R, cc[a], of[a]);
       rec.r0[i] = make_float4(of[0], of[1], of[2], __uint_as_float(c));
