@@ -488,15 +488,13 @@ __device__ __forceinline__ uint32_t walker_key(RowWalker &w, const Grid &g, int 
   return w.tbase + (uint32_t)(x + (y - ty * kTileY) * g.N[0] + (z - tz * kTileZ) * g.N[0] * kTileY);
 }
 
-// Window of row r of the walk (raster order): the sort keys [k0, k1) of the
-// row's cells within the walk's reach, and the row's (y, z) cell; false if
-// the row lies outside the grid or beyond the reach.
+// Window of the row at (dy, dz) cells: the sort keys [k0, k1) of the row's
+// cells within the walk's reach, the row's (y, z) cell and the squared
+// distance to it (in cells, shortened); false if the row lies outside the grid
+// or beyond the reach.
 template <int DIM>
-__device__ __forceinline__ bool walker_row(RowWalker &w, const Grid &g, int r, uint32_t &k0, uint32_t &k1, int &iy,
-                                           int &iz) {
-  const int side = 2 * g.reach + 1;
-  const int dy = (DIM == 3 ? r % side : r) - g.reach;
-  const int dz = DIM == 3 ? r / side - g.reach : 0;
+__device__ __forceinline__ bool walker_row_at(RowWalker &w, const Grid &g, int dy, int dz, uint32_t &k0, uint32_t &k1,
+                                              int &iy, int &iz, float &d2) {
   iy = w.cy + dy;
   iz = w.cz + dz;
   if (iy < 0 || iy >= g.N[1]) return false;
@@ -506,6 +504,7 @@ __device__ __forceinline__ bool walker_row(RowWalker &w, const Grid &g, int r, u
   float ez = DIM == 3 ? (dz > 0 ? (float)dz - w.uz : (dz < 0 ? w.uz - (float)(dz + 1) : 0.0f)) : 0.0f;
   ey = fmaxf(0.0f, ey - kWalkSlack);
   ez = fmaxf(0.0f, ez - kWalkSlack);
+  d2 = ey * ey + ez * ez;
   const float rem = w.rr2 - ey * ey - ez * ez;
   if (rem < 0.0f) return false;
   const float reach = __builtin_amdgcn_sqrtf(rem) + kWalkSlack;  // hardware sqrt (~1 ulp), covered by the slack
@@ -517,6 +516,16 @@ __device__ __forceinline__ bool walker_row(RowWalker &w, const Grid &g, int r, u
   k0 = walker_key(w, g, x0, iy, iz);
   k1 = k0 + (uint32_t)(x1 - x0) + 1u;  // x-row cells are consecutive keys
   return true;
+}
+
+// The same for row r of the walk (raster order).
+template <int DIM>
+__device__ __forceinline__ bool walker_row(RowWalker &w, const Grid &g, int r, uint32_t &k0, uint32_t &k1, int &iy,
+                                           int &iz) {
+  const int side = 2 * g.reach + 1;
+  float d2;
+  return walker_row_at<DIM>(w, g, (DIM == 3 ? r % side : r) - g.reach, DIM == 3 ? r / side - g.reach : 0, k0, k1, iy,
+                            iz, d2);
 }
 
 // Fluid runs [lo[r], hi[r]) of all NR rows of the walk (NR = (2 reach +

@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) k_mirror_f64(Phys P, Grid g, Dummies d, i
     const double xd = d.x[0][k], yd = d.x[1][k], zd = DIM == 3 ? d.x[2][k] : 0.0;
     RowWalker w;
     walker_init<DIM>(w, g, xd, yd, zd, P.win);
-    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, P.two_h2, [&](uint32_t q) {
+    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, P.two_h2, P.win - P.two_h, [&](uint32_t q) {
       const double4 b = rec0[q];
       return dist2_exact<DIM>(b.x - xd, b.y - yd, b.z - zd);
     });

@@ -1,6 +1,7 @@
 """The wall mirror on both sides of its dispatch (one lane or a team of lanes
 per wall particle, 131,072 wall particles apart) with one, two and three cells
-searched on each side: 9, 25 and 49 rows, in rounds of 13 or 32.  Against the
+searched on each side: 9, 25 and 49 rows, on a jittered lattice and on a plain
+one, whose equidistant sources are told apart by their index.  Against the
 oracle at the parity bars (sources exact, values and rates 1e-12)."""
 import numpy as np
 import pytest
@@ -12,17 +13,20 @@ from test_gpu_parity import _flags_all, compare_rates
 pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore::RuntimeWarning")]
 
 
+@pytest.mark.parametrize("jitter", [0.1, 0.0])
 @pytest.mark.parametrize("layers,reach", [(3, 3), (9, 1), (9, 2), (9, 3)])
-def test_mirror_dispatch(layers, reach):
+def test_mirror_dispatch(layers, reach, jitter):
     from paper_2608_22269_amd import Simulation
     case = wl.box3d(0.02, (1.0, 0.9, 0.9), (1.0, 0.9, 0.1), layers=layers, **_flags_all())
-    case = wl.random_velocity(wl.jitter(case, 0.1, 21), 0.05, 22)
+    case = wl.random_velocity(wl.jitter(case, jitter, 21) if jitter else case, 0.05, 22)
     case = wl.with_params(case, cell_size=2.0 * case["params"]["h"] / reach)
     assert ((case["kind"] != 0).sum() > 131072) == (layers == 9)
     sim = Simulation(case)
     sim.eval_rates()
     compare_rates(sim, case, oracle.eval_rates(case))
     sim.close()
+    if not jitter:
+        return
     mixed = wl.with_params(case, precision="mixed")
     sm = Simulation(mixed)
     sm.eval_rates()
