@@ -296,7 +296,7 @@ hipError_t launch_mirror_mixed(const Phys &P, const Grid &g, const Dummies &d, i
                                const uint32_t *cs_f, uint32_t nf, const Scalars *sc, hipStream_t s,
                                const uint32_t *fid) {
   if (nd <= 0) return hipSuccess;
-  const bool team = nd <= kMirrorTeamRows;
+  const bool team = nd <= kMirrorTeamRowsMixed;
 #define WB_GO(D, T) \
   hipLaunchKernelGGL((k_mirror_mixed<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec, cs_f, nf, sc, fid)
   if (P.dim == 2 && team) WB_GO(2, kMirrorTeam);
