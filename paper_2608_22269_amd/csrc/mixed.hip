@@ -601,12 +601,12 @@ __device__ __forceinline__ void abs32_body(const MixedI &I, const float4 &xi, co
 // 2h + skin, tagged skin candidates skipped by the body, non-empty list
 // fills kept in kl.
 template <int DIM, bool PST4, bool KEEP, bool ABS = false>
-__global__ void __launch_bounds__(256) WB_MIXED_ATTR
+__global__ void __launch_bounds__(kSearchBlock) WB_MIXED_ATTR
     k_pair_mixed(Phys P, Grid g, MixedRec rec, const uint32_t *__restrict__ cs_f, const uint32_t *__restrict__ cs_d,
                  uint32_t nf, Scalars *sc, Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
-  __shared__ uint32_t list[kMList][kBlock];
+  __shared__ uint32_t list[kMList][kSearchBlock];
   const int tid = threadIdx.x;
-  const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kBlock + tid;
+  const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kSearchBlock + tid;
   const bool active = i < nf;
 
   float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0, axa = a0;
@@ -627,7 +627,7 @@ __global__ void __launch_bounds__(256) WB_MIXED_ATTR
   // this lane's kept-list bookkeeping in LDS (packed chunk counts, chunks
   // so far at bit kKeptNchShift, saturating at 15): touched once per fill,
   // it holds no registers through the search
-  __shared__ unsigned long long kbook[KEEP ? kBlock : 1];
+  __shared__ unsigned long long kbook[KEEP ? kSearchBlock : 1];
   if (KEEP) kbook[tid] = 0ull;
 
   PairSums S;
@@ -729,7 +729,7 @@ __global__ void __launch_bounds__(256) WB_MIXED_ATTR
   coop_init(cw, g, active, (float)rho, DIM);
   for (;;) {
     const bool fin =
-        coop_fill<DIM, kMList, kMBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kBlock, cnt, S.ntest, load, near);
+        coop_fill<DIM, kMList, kMBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kSearchBlock, cnt, S.ntest, load, near);
     run_list(cnt);
     cnt = 0;
     if (fin) break;
@@ -813,7 +813,8 @@ template <int DIM>
 void launch_pair_mixed_inst(const Phys &P, const Grid &g, const MixedRec &rec, const uint32_t *cs_f,
                             const uint32_t *cs_d, uint32_t nf, Scalars *sc, const Rates &out, uint32_t *cand,
                             const KeptLists &kl, int mode, bool abs32, hipStream_t s) {
-  dim3 gr(grid_for(nf)), bl(kBlock);
+  const int block = mode == kPairKept ? kBlock : kSearchBlock;
+  dim3 gr(grid_for(nf, block)), bl(block);
   const bool p4 = P.pst_n == 4.0;
   if (abs32) {
     if (mode == kPairSearch) {

@@ -191,13 +191,13 @@ __device__ __forceinline__ void pair_body_f64(const Phys &P, const double4 &a0, 
 // for the later right-hand sides; a lane with more than kKeepChunks fills
 // raises sc->vovf.
 template <int DIM, bool PST4, bool KEEP>
-__global__ void __launch_bounds__(256) WB_PAIR_ATTR k_pair_f64(Phys P, Grid g, const double4 *__restrict__ rec0,
+__global__ void __launch_bounds__(kSearchBlock) WB_PAIR_ATTR k_pair_f64(Phys P, Grid g, const double4 *__restrict__ rec0,
                                                   const double4 *__restrict__ rec1, const uint32_t *__restrict__ cs_f,
                                                   const uint32_t *__restrict__ cs_d, uint32_t nf, Scalars *sc,
                                                   Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
-  __shared__ uint32_t list[kList][kBlock];
+  __shared__ uint32_t list[kList][kSearchBlock];
   const int tid = threadIdx.x;
-  const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kBlock + tid;
+  const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kSearchBlock + tid;
   const bool active = i < nf;
 
   double4 a0 = make_double4(0.0, 0.0, 0.0, 0.0), a1 = a0;
@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(256) WB_PAIR_ATTR k_pair_f64(Phys P, Grid g, c
   // this lane's kept-list bookkeeping in LDS (packed chunk counts, chunks
   // so far at bit kKeptNchShift, saturating at 15): touched once per fill,
   // it holds no registers through the search
-  __shared__ unsigned long long kbook[KEEP ? kBlock : 1];
+  __shared__ unsigned long long kbook[KEEP ? kSearchBlock : 1];
   if (KEEP) kbook[tid] = 0ull;
 
   // consume the first cnt entries of this lane's list
@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(256) WB_PAIR_ATTR k_pair_f64(Phys P, Grid g, c
   CoopWalk cw;
   coop_init(cw, g, active, (float)rho, DIM);
   for (;;) {
-    const bool fin = coop_fill<DIM, kList, kBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kBlock, cnt, S.ntest,
+    const bool fin = coop_fill<DIM, kList, kBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kSearchBlock, cnt, S.ntest,
                                                    load, near);
     run_list(cnt);
     cnt = 0;
@@ -434,10 +434,10 @@ __device__ __forceinline__ const double4 &rec_at(const double4 *rec, uint32_t j)
 // indices are first listed in LDS, so that the short rows fill the lanes (the
 // other way round 928 against 637 us at 651,000 particles, cells of 2h, and 710
 // against 565, cells of h; in 2D both take the same).  Neighbour number n goes to lane n mod 8 wherever the list is
-// emptied, so a plain search, one that keeps its candidates (kPairSearchKeep:
-// radius 2h + skin) and the pass from kept candidates (kPairKept, lists built
-// by this kernel only: full chunks but the last) give the same sums bit for
-// bit.
+// emptied, so this kernel's plain search, the one that keeps its candidates
+// (kPairSearchKeep: radius 2h + skin) and its pass from kept candidates
+// (kPairKept, lists built by this kernel only: full chunks but the last) give
+// the same sums bit for bit.
 // Everything that crosses lanes sits under scalar control flow: trip counts
 // come from ballots and lane reads, and list stores are unconditional (a lane
 // without an entry stores to a spare slot).  A conditional store before a loop
@@ -620,32 +620,34 @@ k_pair_team_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 
 
 // Whether the pass runs by teams: up to the count where one lane per particle
 // (k_pair_f64, k_pair_kept_f64) catches up.  With a lane each, a wave's chain
-// of loads takes 240 us in 3D (36 us in 2D) whatever the count, and the waves
-// come in rounds of 4,096; with a lane each the instructions per particle are
-// fewer.  Measured, us, lane / team: 3D search, cells of h 251 / 35 (17,500
-// particles), 769 / 567 (651,000), 2,240 / 1,543 (1.76M), 4,445 / 4,510 (5.2M);
-// cells of 2h 263 / 41, 865 / 637, 2,112 / 1,743, 5,276 / 5,169; building lists
-// 293 / 45, 978 / 818, 2,056 / 2,244; from kept lists 64 / 23, 83 / 55 (70,400),
-// 113 / 124 (193,000).  2D search 37 / 12 (5,000), 41 / 28 (80,000), 46 / 46
-// (155,000); from kept lists 16 / 11 (20,000), 20 / 25 (80,000).  The plain
-// search and the one that builds lists change over at the same count, so that
-// their sums are the same bit for bit.
+// of loads takes 230 us in 3D (36 us in 2D) whatever the count, and the waves
+// come in rounds of 4,096; the team spends more instructions per particle.
+// Measured, us, lane / team: 3D search, cells of h 234 / 35 (17,500 particles),
+// 675 / 575 (651,000), 2,102 / 1,536 (1.76M), 2,912 / 2,641 (3.0M); cells of 2h
+// 251 / 41, 823 / 638, 2,053 / 1,739, 3,130 / 2,996; building lists (a team's
+// lanes store a particle's entries 256 bytes apart) 275 / 48, 862 / 825, 1,264
+// / 1,430 (1.12M), 1,835 / 2,250; from kept lists 65 / 24, 83 / 55 (70,400),
+// 111 / 126 (193,000).  2D search 36 / 12 (5,000), 40 / 28 (80,000), 47 / 47
+// (155,000); from kept lists 16 / 11 (20,000), 20 / 26 (80,000).
 template <int DIM>
 static bool by_team(uint32_t nf, int64_t nrec, int mode) {
   if (nrec > (int64_t)1 << 27) return false;  // rec_at's offsets
   if (mode == kPairKept) return nf <= (DIM == 3 ? 130000u : 40000u);  // within the next line: lists of this kernel
-  return nf <= (DIM == 3 ? 2000000u : 120000u);
+  if (mode == kPairSearchKeep) return nf <= (DIM == 3 ? 700000u : 120000u);
+  return nf <= (DIM == 3 ? 3000000u : 120000u);
 }
 
 template <int DIM>
 void launch_pair_f64_inst(const Phys &P, const Grid &g, const double4 *rec0, const double4 *rec1,
                           const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, int64_t nrec, Scalars *sc,
                           const Rates &out, uint32_t *cand, const KeptLists &kl, int mode, hipStream_t s) {
-  dim3 gr(grid_for(nf)), bl(kBlock);
+  const int block = mode == kPairKept ? kBlock : kSearchBlock;
+  dim3 gr(grid_for(nf, block)), bl(block);
   const bool p4 = P.pst_n == 4.0;
   if (by_team<DIM>(nf, nrec, mode)) {
     const bool lng = DIM == 3 && g.reach == 1;
     gr = dim3(grid_for(nf, kTeamRows));
+    bl = dim3(kBlock);
 #define WB_TEAM(MODE, LONG)                                                                                       \
   do {                                                                                                            \
     if (p4)                                                                                                       \

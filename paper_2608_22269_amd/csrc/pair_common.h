@@ -10,6 +10,14 @@
 
 namespace wb {
 
+// Threads of a block of the searching passes.  A block's LDS lists are held
+// until its last wave ends, and the waves end at different times: with one wave
+// per block the CUs hold 16 waves instead of 12 (17.5M particles, building
+// lists: FP64 17.1 -> 15.8 ms; 2.0M in fp32 2.31 -> 1.96; 424,000 mixed, no
+// lists, 0.50 -> 0.46).  The passes from kept lists gather from more places at
+// once then and get slower (8.9 -> 9.2 ms): they keep blocks of kBlock.
+constexpr int kSearchBlock = 64;
+
 __device__ __forceinline__ uint32_t wave_append(uint32_t *counter, bool pred) {
   // wave-aggregated atomic append; returns the slot of this lane (valid if pred)
   unsigned long long mask = __ballot(pred);

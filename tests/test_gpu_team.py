@@ -1,6 +1,7 @@
 """The FP64 pair pass at the edges of its dispatch: teams of 8 lanes per
-particle (blocks of 32 particles) up to 2,000,000 particles in 3D and 120,000
-in 2D, 130,000 and 40,000 from kept lists, one lane per particle beyond; over
+particle (blocks of 32 particles) up to 3,000,000 particles in 3D and 120,000
+in 2D, 700,000 and 120,000 where it builds lists, 130,000 and 40,000 from kept
+lists, one lane per particle beyond; over
 cells of 2h in 3D the rows are tested in place, else listed.  Against the
 oracle at the parity bars; the changeovers that the oracle cannot reach
 against the same right-hand side over other cells or without lists."""
@@ -87,12 +88,13 @@ def test_changeover_2d(n):
     sim.close()
 
 
-@pytest.mark.parametrize("dim,n", [(2, 39999), (2, 40001), (3, 129999), (3, 130001)])
+@pytest.mark.parametrize("dim,n", [(2, 39999), (2, 40001), (3, 129999), (3, 130001), (3, 700000), (3, 700001)])
 def test_changeover_from_kept_lists(dim, n):
-    """Lists built by teams, then read by teams or by a lane per particle:
-    two steps against the path that searches at every stage."""
+    """Lists built and read by teams, built by teams and read by a lane per
+    particle, and both by a lane: two steps against the path that searches at
+    every stage."""
     if dim == 3:
-        case = _block(n, dx=0.012, seed=1)
+        case = _block(n, dx=0.012 if n < 200000 else 0.0105, seed=1)
     else:
         case = wl.tank2d(dx=0.0035, **_flags_all())
         fluid = np.nonzero(case["kind"] == 0)[0]
@@ -100,7 +102,7 @@ def test_changeover_from_kept_lists(dim, n):
         drop = np.isin(np.arange(len(case["kind"])), fluid[np.argsort(case["x"][fluid, 1])[n:]])
         case = dict(case, **{k: case[k][~drop] for k in ("x", "u", "phi", "kind", "normal")})
         case = wl.random_velocity(case, 0.02, 3)
-    case = wl.with_params(case, cell_size=2.1 * case["params"]["h"])
+    case = wl.with_params(case, cell_size=(2.1 if n < 200000 else 1.03) * case["params"]["h"])
     keep, plain = _sim(wl.with_params(case, keep_lists=True)), _sim(case)
     assert keep.nf == n
     for s in (keep, plain):
@@ -112,12 +114,11 @@ def test_changeover_from_kept_lists(dim, n):
         s.close()
 
 
-@pytest.mark.parametrize("n", [2000000, 2000001])
+@pytest.mark.parametrize("n", [3000000, 3000001])
 def test_changeover_3d(n):
-    """Around 2,000,000 particles: cells of h against cells of 2h, whose
-    windows, lists and orders of summation differ, and with lists (cells with
-    room) the build's sums."""
-    case = _block(n, dx=0.0075, seed=4)
+    """Around 3,000,000 particles: cells of h against cells of 2h, whose
+    windows, lists and orders of summation differ."""
+    case = _block(n, dx=0.0065, seed=4)
     h = case["params"]["h"]
     a, b = _sim(wl.with_params(case, cell_size=h)), _sim(wl.with_params(case, cell_size=2.0 * h))
     for s in (a, b):
