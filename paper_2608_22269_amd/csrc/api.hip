@@ -1061,8 +1061,14 @@ sph_status sph_step(sph_ctx *c, int32_t nsteps, double dt_override) {
   if (nsteps < 0 || !std::isfinite(dt_override)) return fail(c, SPH_EINVAL, "bad nsteps or dt_override");
   if ((c->p.flags & SPH_F_GRAPH) && !c->profiling && nsteps >= 2) {
     if (!graph_matches(c, dt_override)) st = graph_capture(c, dt_override);
-    for (; nsteps >= 2 && st == SPH_OK; nsteps -= 2)
+    for (; nsteps >= 2 && st == SPH_OK; nsteps -= 2) {
       st = hip_check(c, hipGraphLaunch(c->gexec, c->s), "graph launch");
+      // a replay runs no host code: the flags as one_step leaves them (an even
+      // number of sorts outside sph_step brings the buffers back to where the
+      // graph wants them, with cells_current set)
+      c->cells_current = c->lists_valid = c->recs_fresh = false;
+      c->rates_current = c->umax_fresh = true;
+    }
   }
   for (int32_t k = 0; k < nsteps && st == SPH_OK; ++k) st = one_step(c, dt_override);
   return st;

@@ -94,3 +94,30 @@ def test_graph_with_the_learned_detector(Sim):
     a.step(4)
     b.step(4)
     _same(a, b)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "fp32"])
+def test_replay_after_two_sorts_outside_the_step(Sim, precision):
+    """Two sorts between two replays bring the swapped buffers back to where
+    the captured steps want them: the graph is replayed as it is, and what
+    follows must sort the state it left."""
+    case = wl.with_params(CASES[0][1], precision=precision)
+    a = Sim(case)
+    b = Sim(wl.with_params(case, graph=True))
+    for s in (a, b):
+        s.step(2)
+    for _ in range(3):
+        for s in (a, b):
+            s.eval_rates()
+            s.build_cells()
+            s.step(2)
+        _same(a, b)  # the rates of the replayed steps, not refused
+        for s in (a, b):
+            if precision == "fp64":
+                s.nb = s.neighbors()
+            s.eval_rates()
+        _same(a, b)
+        if precision == "fp64":
+            assert np.array_equal(a.nb[0], b.nb[0]) and np.array_equal(a.nb[1], b.nb[1])
+    for s in (a, b):
+        s.close()
