@@ -39,6 +39,29 @@ def _upload(*arrays):
     return [t], [t.data_ptr() + 4 * int(o) for o in at[:-1]]
 
 
+def _lend(stream, *tensors):
+    """Before a launch on `stream`, if that is not the current one: it starts
+    after what the current stream has been given, and the memory of the
+    tensors (None: skipped), which belongs to the current stream, is not given
+    away there while `stream` still works on it."""
+    import torch
+    cur = torch.cuda.current_stream()
+    if stream == cur:
+        return
+    stream.wait_stream(cur)
+    for t in tensors:
+        if t is not None:
+            t.record_stream(stream)
+
+
+def _returned(stream):
+    """After a launch on `stream`: the current stream waits for it."""
+    import torch
+    cur = torch.cuda.current_stream()
+    if stream != cur:
+        cur.wait_stream(stream)
+
+
 class MLPTrainer:
     """FP32 trainer (hand-written HIP forward, backward and Adam kernels)."""
 
@@ -51,6 +74,7 @@ class MLPTrainer:
             raise L.SphError(L.SPH_EINVAL, "sph_mlp_workspace_bytes")
         self._ws, ptr = device_buffer(nbytes)
         self.stream = stream if stream is not None else torch.cuda.current_stream()
+        _lend(self.stream, self._ws)
         p0 = np.ascontiguousarray(params0, dtype=np.float32)
         mu = np.ascontiguousarray(mean, dtype=np.float32)
         sd = np.ascontiguousarray(std, dtype=np.float32)
@@ -76,8 +100,10 @@ class MLPTrainer:
     def forward(self, X):
         X = _dev(X, self.torch.float32)
         out = self.torch.empty(X.shape[0], dtype=self.torch.float32, device="cuda")
+        _lend(self.stream, X, out)
         _check(L.lib().sph_mlp_forward(self.h, C.c_void_p(X.data_ptr()), X.shape[0], C.c_void_p(out.data_ptr())),
                "sph_mlp_forward")
+        _returned(self.stream)
         return out.cpu().numpy()
 
     def loss_grad(self, X, y, w=None):
@@ -87,10 +113,12 @@ class MLPTrainer:
         wd = None if w is None else _dev(w, torch.float32)
         loss = torch.empty(1, dtype=torch.float32, device="cuda")
         grad = torch.empty(NPARAM, dtype=torch.float32, device="cuda")
+        _lend(self.stream, X, y, wd, loss, grad)
         _check(L.lib().sph_mlp_loss_grad(self.h, C.c_void_p(X.data_ptr()), C.c_void_p(y.data_ptr()),
                                          C.c_void_p(wd.data_ptr()) if wd is not None else None, X.shape[0],
                                          C.c_void_p(loss.data_ptr()), C.c_void_p(grad.data_ptr())),
                "sph_mlp_loss_grad")
+        _returned(self.stream)
         return float(loss.item()), grad.cpu().numpy()
 
     def adam(self, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8):
@@ -99,6 +127,7 @@ class MLPTrainer:
     def train_epoch(self, Xd, yd, wd, perm_d, batch, lr):
         """One epoch over device tensors (X n x 16 f32, y, w f32, perm int32)."""
         ml = C.c_float(0.0)
+        _lend(self.stream, Xd, yd, wd, perm_d)
         _check(L.lib().sph_mlp_train_epoch(self.h, C.c_void_p(Xd.data_ptr()), C.c_void_p(yd.data_ptr()),
                                            C.c_void_p(wd.data_ptr()) if wd is not None else None,
                                            C.c_void_p(perm_d.data_ptr()), Xd.shape[0], int(batch), float(lr),
@@ -112,31 +141,31 @@ class MLPTrainer:
 
 
 def infer_bf16(params, mean, std, X, stream=None):
-    """Logits of the rows of X with BF16 MFMA inference (device tensors or arrays)."""
-    import torch
-    hold, (w, mu, sd) = _upload(params, mean, std)  # noqa: F841 (alive until the launch)
-    Xd = X if isinstance(X, torch.Tensor) else _dev(X, torch.float32)
-    out = torch.empty(Xd.shape[0], dtype=torch.float32, device="cuda")
-    s = stream if stream is not None else torch.cuda.current_stream()
-    _check(L.lib().sph_mlp_infer_bf16(C.c_void_p(w), C.c_void_p(mu), C.c_void_p(sd),
-                                      C.c_void_p(Xd.data_ptr()), Xd.shape[0], C.c_void_p(out.data_ptr()),
-                                      C.c_void_p(s.cuda_stream)), "sph_mlp_infer_bf16")
-    return out
+    """Logits of the rows of X with BF16 MFMA inference (device tensors or
+    arrays), on `stream` (the current one) and ready in its order."""
+    return _logits(L.lib().sph_mlp_infer_bf16, "sph_mlp_infer_bf16", params, mean, std, X, stream)
 
 
 def forward_noalloc(params, mean, std, X, stream=None):
     """FP32 logits of the rows of X through sph_mlp_forward_noalloc (the
     trainer's forward pass without a trainer or workspace; at most
-    SPH_MLP_NOALLOC_MAX_ROWS rows).  Returns a device tensor."""
+    SPH_MLP_NOALLOC_MAX_ROWS rows), on `stream` (the current one) and ready in
+    its order.  Returns a device tensor."""
+    return _logits(L.lib().sph_mlp_forward_noalloc, "sph_mlp_forward_noalloc", params, mean, std, X, stream)
+
+
+def _logits(call, what, params, mean, std, X, stream):
     import torch
-    hold, (w, mu, sd) = _upload(params, mean, std)  # noqa: F841 (alive until the launch)
+    hold, (w, mu, sd) = _upload(params, mean, std)
     Xd = X if isinstance(X, torch.Tensor) else _dev(X, torch.float32)
     out = torch.empty(Xd.shape[0], dtype=torch.float32, device="cuda")
-    s = stream if stream is not None else torch.cuda.current_stream()
-    _check(L.lib().sph_mlp_forward_noalloc(C.c_void_p(w), C.c_void_p(mu), C.c_void_p(sd),
-                                           C.c_void_p(Xd.data_ptr()), Xd.shape[0],
-                                           C.c_void_p(out.data_ptr()), C.c_void_p(s.cuda_stream)),
-           "sph_mlp_forward_noalloc")
+    if stream is None:
+        s = torch.cuda.current_stream()
+    else:
+        s = stream
+        _lend(s, *hold, Xd, out)
+    _check(call(C.c_void_p(w), C.c_void_p(mu), C.c_void_p(sd), C.c_void_p(Xd.data_ptr()), Xd.shape[0],
+                C.c_void_p(out.data_ptr()), C.c_void_p(s.cuda_stream)), what)
     return out
 
 
