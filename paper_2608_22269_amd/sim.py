@@ -67,6 +67,11 @@ class Simulation:
         self.device = torch.device(device)
         self._ws, ptr = device_buffer(nbytes, self.device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        if self.stream != torch.cuda.current_stream(self.device):
+            # the workspace's memory belongs to the current stream: ours starts
+            # after it, and it is not given away there while ours works on it
+            self.stream.wait_stream(torch.cuda.current_stream(self.device))
+            self._ws.record_stream(self.stream)
         x = np.ascontiguousarray(case["x"], dtype=np.float64)
         u = np.ascontiguousarray(case["u"], dtype=np.float64)
         phi = np.ascontiguousarray(case["phi"], dtype=np.float64)

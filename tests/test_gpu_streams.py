@@ -66,3 +66,32 @@ def test_trainer_on_a_side_stream(load):
     assert not busy or other.data_ptr() != ptr
     side.synchronize()
     del held, other
+
+
+def test_simulation_on_a_side_stream(load):
+    """Steps queued behind other work on a side stream, the context dropped
+    before they have run: its workspace is not handed out meanwhile, and the
+    field they export last is that of the current stream's steps."""
+    import torch
+    import workloads as wl
+    from paper_2608_22269_amd import Simulation
+    case = wl.random_velocity(wl.tank2d(dx=0.02), 0.05, 3)
+    a = Simulation(case)
+    a.step(3)
+    ref = a.field("x")
+    side = torch.cuda.Stream()
+    b = Simulation(case, stream=side)
+    out = torch.zeros(ref.shape, dtype=torch.float64, device="cuda")
+    held = _busy(side, load)
+    b.step(3)
+    b.field_device("x", out)
+    ptr, nbytes = b._ws.data_ptr(), b._ws.numel()
+    b.close()
+    del b
+    other = torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)
+    busy = not side.query()
+    assert not busy or other.data_ptr() != ptr
+    side.synchronize()
+    assert np.array_equal(out.cpu().numpy(), ref)
+    a.close()
+    del held, other
