@@ -31,7 +31,7 @@ __device__ __forceinline__ int64_t nearest_fluid(RowWalker &w, const Grid &g, co
   uint32_t best = 0xffffffffu, best_id = 0;
   Real best_r2 = limit;
   auto take = [&](uint32_t j, Real r2) {
-    if (r2 > best_r2) return;
+    if (!(r2 <= best_r2)) return;  // nor a particle at NaN
     const uint32_t id = fid[j];
     if (best == 0xffffffffu || r2 < best_r2 || id < best_id) {
       best = j;

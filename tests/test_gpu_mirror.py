@@ -36,3 +36,37 @@ def test_mirror_dispatch(layers, reach, jitter):
     # FP32 distances may swap two nearly equidistant sources
     assert (sm.field("mirror_src")[d] != src[d]).sum() <= 1e-3 * d.sum()
     sm.close()
+
+
+@pytest.mark.parametrize("nd", [40, 90100])
+def test_no_source_at_nan(nd):
+    """A particle whose position has become NaN is kept in cell 0 until the
+    error is reported; wall particles around that cell, out of reach of any
+    fluid, must not take it for their source (a field exported to the device
+    does not wait for the error)."""
+    import torch
+    from paper_2608_22269_amd import Simulation, _lib as L
+    dx = 0.01
+    rng = np.random.default_rng(3)
+    pd = wl.base_params(2, dx, domain_lo=[0.0] * 3, domain_hi=[1.0, 1.0, 0.0], depth=0.1)
+    g = np.stack(np.meshgrid(np.arange(10), np.arange(10), indexing="ij"), -1).reshape(-1, 2)
+    xf, xd = 0.5 + dx * g, rng.uniform(0.0, 4.0 * pd["h"], (nd, 2))
+    phi = np.zeros(100 + nd)
+    phi[55] = 800.0 * pd["c0"] ** 2  # its density overflows
+    normal = np.zeros((100 + nd, 2))
+    normal[100:, 1] = 1.0
+    case = {"params": pd, "x": np.concatenate([xf, xd]), "u": np.zeros((100 + nd, 2)), "phi": phi,
+            "kind": np.repeat(np.array([0, 1], np.uint8), [100, nd]), "normal": normal, "mass": None, "t": 0.0,
+            "meta": {}}
+    sim = Simulation(case)
+    sim.step(2, dt=1e-4)
+    x = torch.zeros((sim.n, 2), dtype=torch.float64, device="cuda")
+    src = torch.zeros(sim.n, dtype=torch.int32, device="cuda")
+    sim.field_device("x", x)
+    sim.field_device("mirror_src", src)
+    torch.cuda.synchronize()
+    assert torch.isnan(x[:100]).any()
+    assert (src[100:] == -1).all()
+    with pytest.raises(L.SphError):
+        sim.sync()
+    sim.close()
