@@ -227,7 +227,10 @@ __global__ void __launch_bounds__(256) k_mirror_mixed(Phys P, Grid g, Dummies d,
     const float xf = (float)xd, yf = (float)yd, zf = (float)zd;
     RowWalker w;
     walker_init<DIM>(w, g, xd, yd, zd, P.win);
-    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, (float)P.two_h2, P.win - P.two_h, [&](uint32_t q) {
+    // skin_pad: above the rounding of the FP32 positions, which far from the
+    // origin is many thousandths of a cell
+    const double extra = P.win - P.two_h + P.skin_pad;
+    const int64_t j = nearest_fluid<DIM, T>(w, g, cs_f, fid, (float)P.two_h2, extra, [&](uint32_t q) {
       const float4 b = rec.xa[q];
       const float dxv = b.x - xf, dyv = b.y - yf, dzv = DIM == 3 ? b.z - zf : 0.f;
       const float s = fmaf(dxv, dxv, dyv * dyv);

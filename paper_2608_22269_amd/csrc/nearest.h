@@ -21,9 +21,10 @@ constexpr int64_t kMirrorTeamRows = 90000, kMirrorTeamRowsMixed = 150000;
 // Index of the fluid particle with the smallest squared distance d2(j) <=
 // limit (ties: lower original index fid), -1 if none.  The own row and those
 // around it come first, then the rows ring by ring, once a particle is found
-// only as far as that one lies (extra: what the cells may be off by, in
-// metres): of some 190 particles within reach a few dozen are looked at.  The
-// T lanes of a team get the same result.  The whole wave calls it.
+// only as far as that one lies (extra: what the cells may be off by and, where
+// d2 is from FP32 positions, what those are rounded by, in metres): of some
+// 190 particles within reach a few dozen are looked at.  The T lanes of a team
+// get the same result.  The whole wave calls it.
 template <int DIM, int T, class Real, class Dist>
 __device__ __forceinline__ int64_t nearest_fluid(RowWalker &w, const Grid &g, const uint32_t *__restrict__ cs_f,
                                                  const uint32_t *__restrict__ fid, Real limit, double extra, Dist d2) {
@@ -49,7 +50,7 @@ __device__ __forceinline__ int64_t nearest_fluid(RowWalker &w, const Grid &g, co
     }
   };
   // a particle no farther than the best one lies in no row or cell beyond
-  // it, widened by extra and by 0.002 cells for positions in FP32
+  // it, widened by extra and by 0.002 cells for the rounding here
   auto shrink = [&]() {
     if (best == 0xffffffffu) return;
     const float r = sqrtf((float)best_r2) * (float)g.invR + (float)(extra * g.invR) + 0.002f;

@@ -70,3 +70,55 @@ def test_no_source_at_nan(nd):
     with pytest.raises(L.SphError):
         sim.sync()
     sim.close()
+
+
+def _far_pairs(copies, seed=0):
+    """Wall particles 1,000 m (100,000 cells of h) from the origin, where FP32
+    positions lie 0.006 cells apart, `copies` on each place.  Each has two
+    fluid particles: one in its own row of cells, nearer by a few thousandths
+    of a cell or as far as the other, which lies just inside the second row
+    above."""
+    rng = np.random.default_rng(seed)
+    h = 0.01
+    pd = wl.base_params(2, h / 1.3, domain_lo=[1000.0, 1000.0, 0.0], domain_hi=[1003.6, 1000.5, 0.0], depth=0.1,
+                        precision="mixed")
+    pd = dict(pd, h=h, cell_size=h)
+    lo = np.array(pd["domain_lo"][:2])
+    c = np.stack(np.meshgrid(4 + 6 * np.arange(58), 4 + 6 * np.arange(7), indexing="ij"), -1).reshape(-1, 2)
+    d = lo + (c + np.stack([rng.uniform(0.3, 0.7, len(c)), np.full(len(c), 0.5)], 1)) * h
+    above = d + np.stack([np.zeros(len(c)), rng.uniform(1.5005, 1.506, len(c))], 1) * h
+    beside = d + np.stack([rng.uniform(1.490, 1.504, len(c)), np.zeros(len(c))], 1) * h
+    x = np.concatenate([above, beside, np.repeat(d, copies, axis=0)])
+    nf, n = 2 * len(c), len(x)
+    normal = np.zeros((n, 2))
+    normal[nf:, 1] = 1.0
+    case = {"params": pd, "x": x, "u": np.zeros((n, 2)), "phi": np.zeros(n),
+            "kind": np.repeat(np.array([0, 1], np.uint8), [nf, n - nf]), "normal": normal, "mass": None, "t": 0.0,
+            "meta": {}}
+    # positions as the library stores them: an FP32 offset in the cell, then
+    # FP32; differences and squares of these are exact in FP32
+    corner = lo + np.floor((x[:nf] - lo) / h) * h
+    stored = (corner + (x[:nf] - corner).astype(np.float32)).astype(np.float32)
+    mid = np.abs(np.abs(stored - (corner + (x[:nf] - corner).astype(np.float32))) / np.spacing(stored) - 0.5)
+    sure = (mid > 1e-2).all(1)
+    sure = sure[:nf // 2] & sure[nf // 2:]
+    r2 = ((stored - np.concatenate([d, d]).astype(np.float32)) ** 2).sum(1)
+    src = np.where(r2[:nf // 2] <= r2[nf // 2:], np.arange(nf // 2), np.arange(nf // 2, nf))
+    return case, np.repeat(src, copies), np.repeat(sure, copies)
+
+
+@pytest.mark.parametrize("copies", [1, 400])
+def test_mixed_mirror_far_from_the_origin(copies):
+    """The source is the nearest in FP32 positions (ties: the lower index)
+    also where their rounding is far above a thousandth of a cell: a team of
+    lanes per wall particle, and one lane."""
+    from paper_2608_22269_amd import Simulation
+    case, src, sure = _far_pairs(copies)
+    nd = len(src)
+    assert nd < 90000 if copies == 1 else nd > 150000
+    assert sure.mean() > 0.9
+    sim = Simulation(case)
+    sim.eval_rates()
+    got = sim.field("mirror_src")[-nd:]
+    assert np.array_equal(got[sure], src[sure])
+    sim.close()
