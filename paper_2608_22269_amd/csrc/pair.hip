@@ -622,19 +622,28 @@ k_pair_team_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 
 // (k_pair_f64, k_pair_kept_f64) catches up.  With a lane each, a wave's chain
 // of loads takes 230 us in 3D (36 us in 2D) whatever the count, and the waves
 // come in rounds of 4,096; the team spends more instructions per particle.
-// Measured, us, lane / team: 3D search, cells of h 234 / 35 (17,500 particles),
-// 675 / 575 (651,000), 2,102 / 1,536 (1.76M), 2,912 / 2,641 (3.0M); cells of 2h
-// 251 / 41, 823 / 638, 2,053 / 1,739, 3,130 / 2,996; building lists (a team's
-// lanes store a particle's entries 256 bytes apart) 275 / 48, 862 / 825, 1,264
-// / 1,430 (1.12M), 1,835 / 2,250; from kept lists 65 / 24, 83 / 55 (70,400),
-// 111 / 126 (193,000).  2D search 36 / 12 (5,000), 40 / 28 (80,000), 47 / 47
-// (155,000); from kept lists 16 / 11 (20,000), 20 / 26 (80,000).
+//
+// The two searching passes share a line, so that one that builds lists gives
+// the plain search's sums bit for bit at any count.  In 3D it depends on the
+// cells: lists are built only over those with room for a skin, where the
+// team's building pass falls behind early (its lanes store a particle's
+// entries 256 bytes apart); without room every pass is a plain search.
+//
+// Measured on a sloshing tank, a dam break, a cylinder entry and a cube of
+// water (3D), a tank and a dam break (2D), us, lane / team: 3D plain search,
+// cells of h 529 / 423 (446,000), 1,320 to 1,350 / 1,330 to 1,415 (1.5M),
+// 1,771 / 1,786 and 1,775 / 1,944 (2.1M), 2,033 / 2,228 (2.4M); cells of 2h
+// 649 / 461 (446,000), 2,029 / 1,889 (1.9M), 3,080 to 3,096 / 2,984 to 3,025
+// (3.0M), 4,291 / 4,304 (4.4M), 5,082 / 5,178 (5.2M).  Building lists, cells of
+// 1.02 h 862 / 893 (710,000), 1,257 / 1,400 (1.12M); of 2.05 h 965 / 940
+// (636,000), 1,216 / 1,261 (850,000), 2,040 / 2,325 (1.53M).
 template <int DIM>
-static bool by_team(uint32_t nf, int64_t nrec, int mode) {
+static bool by_team(const Phys &P, const Grid &g, uint32_t nf, int64_t nrec, int mode) {
   if (nrec > (int64_t)1 << 27) return false;  // rec_at's offsets
   if (mode == kPairKept) return nf <= (DIM == 3 ? 130000u : 40000u);  // within the next line: lists of this kernel
-  if (mode == kPairSearchKeep) return nf <= (DIM == 3 ? 700000u : 120000u);
-  return nf <= (DIM == 3 ? 3000000u : 120000u);
+  if (DIM == 2) return nf <= 120000u;
+  const bool room = (double)g.reach * g.R - P.two_h > 1e-6 * g.R;  // as for P.skin_max
+  return nf <= (room ? 700000u : 3000000u);
 }
 
 template <int DIM>
@@ -644,7 +653,7 @@ void launch_pair_f64_inst(const Phys &P, const Grid &g, const double4 *rec0, con
   const int block = mode == kPairKept ? kBlock : kSearchBlock;
   dim3 gr(grid_for(nf, block)), bl(block);
   const bool p4 = P.pst_n == 4.0;
-  if (by_team<DIM>(nf, nrec, mode)) {
+  if (by_team<DIM>(P, g, nf, nrec, mode)) {
     const bool lng = DIM == 3 && g.reach == 1;
     gr = dim3(grid_for(nf, kTeamRows));
     bl = dim3(kBlock);
