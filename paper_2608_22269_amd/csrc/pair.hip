@@ -636,14 +636,20 @@ k_pair_team_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 
 // 649 / 461 (446,000), 2,029 / 1,889 (1.9M), 3,080 to 3,096 / 2,984 to 3,025
 // (3.0M), 4,291 / 4,304 (4.4M), 5,082 / 5,178 (5.2M).  Building lists, cells of
 // 1.02 h 862 / 893 (710,000), 1,257 / 1,400 (1.12M); of 2.05 h 965 / 940
-// (636,000), 1,216 / 1,261 (850,000), 2,040 / 2,325 (1.53M).
+// (636,000), 1,216 / 1,261 (850,000), 2,040 / 2,325 (1.53M).  From kept lists
+// (built by teams, cells of 1.02 h) 49 / 20 (15,000), 52 / 44 and 60 / 64
+// (53,000), 64 / 56 (69,500), 71 / 84 (78,000), 65 / 64 (86,000), 73 / 108
+// (105,000).  2D search, cells of 2h and h within 2 us: 42 / 30 (80,000), 44 /
+// 40 and 42 / 40 (125,000), 47 / 47 and 44 / 46 (152,000); building lists 49 /
+// 45 (125,000), 50 / 52 and 52 / 52 (152,000); from kept lists 15 / 11
+// (20,000), 16 / 16 (33,000 and 36,000), 17 / 20 (41,000).
 template <int DIM>
 static bool by_team(const Phys &P, const Grid &g, uint32_t nf, int64_t nrec, int mode) {
   if (nrec > (int64_t)1 << 27) return false;  // rec_at's offsets
-  if (mode == kPairKept) return nf <= (DIM == 3 ? 130000u : 40000u);  // within the next line: lists of this kernel
+  if (mode == kPairKept) return nf <= (DIM == 3 ? 70000u : 35000u);  // within the next line: lists of this kernel
   if (DIM == 2) return nf <= 120000u;
   const bool room = (double)g.reach * g.R - P.two_h > 1e-6 * g.R;  // as for P.skin_max
-  return nf <= (room ? 700000u : 3000000u);
+  return nf <= (room ? 700000u : g.reach == 1 ? 3000000u : 2000000u);
 }
 
 template <int DIM>
