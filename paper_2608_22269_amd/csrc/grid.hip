@@ -358,10 +358,9 @@ hipError_t launch_sort_keys(const Grid &g, int dim, const double *x, const doubl
     else
       hipLaunchKernelGGL(k_hash_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, g, x, y, z, n, ss.key, ss.slot,
                          ss.count, tsum, sc, ph, q);
-  } else if (q.on) {
-    hipLaunchKernelGGL(k_prep, dim3(1), dim3(1), 0, s, ph, q, sc);
   }
-  hipError_t e = scan_counts(ss, tsum != nullptr, start, g.nkey, s);
+  hipError_t e = n <= 0 && q.on ? launch_prep(ph, q, sc, s) : hipSuccess;
+  if (e == hipSuccess) e = scan_counts(ss, tsum != nullptr, start, g.nkey, s);
   if (e != hipSuccess) return e;
   if (n > 0)
     hipLaunchKernelGGL(k_scatter, dim3(grid_for(std::max(n, ss.tiles))), dim3(kBlock), 0, s, ss.key, ss.slot, start, id,
