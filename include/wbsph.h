@@ -320,7 +320,7 @@ typedef struct sph_mlp sph_mlp;
  * rows.  No GPU is touched. */
 size_t sph_mlp_workspace_bytes(int64_t max_batch);
 
-/* Creates a trainer (FP32 master weights, Adam moments, activations) in the
+/* Creates a trainer (FP32 master weights, Adam moments, gradient sums) in the
  * caller's device workspace; params0 (host, 5,313 floats) is the starting
  * point; mean/std (host, 16 floats) standardise the inputs. */
 sph_status sph_mlp_create(int64_t max_batch, const float *params0, const float *mean,
@@ -370,16 +370,10 @@ sph_status sph_mlp_infer_bf16(const float *params, const float *mean, const floa
  * Same kernel and same logits bit for bit; the weights come from `params`
  * (device, 5,313 floats, the layout of sph_set_classifier), the
  * standardisation from mean/std (device, 16 floats each), rows from X
- * (device, B*16 floats), logits[b] to `logits` (device, B floats).  The
- * activations the kernel stores go to a fixed scratch array inside the
- * library (B <= SPH_MLP_NOALLOC_MAX_ROWS, about 6.8 MB per device, held
- * until the process ends); no device memory is allocated, neither here nor
- * on the first call of a device (which only looks the array up).
- * B > SPH_MLP_NOALLOC_MAX_ROWS or B < 0 -> SPH_EINVAL before any launch; B
- * = 0 -> SPH_OK.  Asynchronous on hip_stream.  Every call on one device
- * shares that device's scratch array: calls that overlap in time on one
- * device (other streams, other threads) race on it and must be ordered by
- * the caller. */
+ * (device, B*16 floats), logits[b] to `logits` (device, B floats).  No device
+ * memory is allocated or kept, and calls share none: they may overlap on any
+ * streams and threads.  B > SPH_MLP_NOALLOC_MAX_ROWS or B < 0 -> SPH_EINVAL
+ * before any launch; B = 0 -> SPH_OK.  Asynchronous on hip_stream. */
 sph_status sph_mlp_forward_noalloc(const float *params, const float *mean, const float *std,
                                    const float *X, int64_t B, float *logits, void *hip_stream);
 

@@ -17,7 +17,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <string>
 
 #include "mlp.h"
@@ -60,43 +59,35 @@ __device__ __forceinline__ void wave_lds_order() {
 
 // ------------------------------------------------------------- training
 
-// Forward for rows[b] = perm ? perm[off + b] : off + b.  blockDim = 256 = four
-// rows, one wave per row, lane = hidden unit.  Stores standardised input,
-// pre-activations and activations for the backward pass; logit to s[b].
+// Logits of B rows of X.  blockDim = 256 = four rows, one wave per row, lane =
+// hidden unit.  Nothing but the logits is stored (the gradient kernel
+// recomputes the activations): 68 bytes a row instead of 900.
 __global__ void __launch_bounds__(256) k_mlp_fwd(const float *__restrict__ w, const float *__restrict__ mean,
                                                  const float *__restrict__ std, const float *__restrict__ X,
-                                                 const int32_t *__restrict__ perm, int64_t off, int64_t B,
-                                                 float *__restrict__ xs, float *__restrict__ z1,
-                                                 float *__restrict__ z2, float *__restrict__ a2,
-                                                 float *__restrict__ s) {
+                                                 int64_t B, float *__restrict__ s) {
   __shared__ float sx[4][kMlpIn];
   __shared__ float sa1[4][kMlpHid];
   const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
   const int64_t b = (int64_t)blockIdx.x * 4 + r;
   const bool on = b < B;
-  const int64_t row = on ? (perm ? (int64_t)perm[off + b] : off + b) : 0;
-  if (on && lane < kMlpIn) {
-    float v = (X[row * kMlpIn + lane] - mean[lane]) / std[lane];
-    sx[r][lane] = v;
-    xs[b * kMlpIn + lane] = v;
-  }
+  if (on && lane < kMlpIn) sx[r][lane] = (X[b * kMlpIn + lane] - mean[lane]) / std[lane];
   __syncthreads();
   float z = w[kOffB1 + lane];
   for (int i = 0; i < kMlpIn; ++i) z += sx[r][i] * w[kOffW1 + i * kMlpHid + lane];
-  if (on) z1[b * kMlpHid + lane] = z;
   sa1[r][lane] = gelu_f(z);
   __syncthreads();
   float y = w[kOffB2 + lane];
   for (int k = 0; k < kMlpHid; ++k) y += sa1[r][k] * w[kOffW2 + k * kMlpHid + lane];
-  const float act = gelu_f(y);
-  if (on) {
-    z2[b * kMlpHid + lane] = y;
-    a2[b * kMlpHid + lane] = act;
-  }
-  float p = act * w[kOffW3 + lane];
+  float p = gelu_f(y) * w[kOffW3 + lane];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) p += __shfl_xor(p, o, 64);
   if (on && lane == 0) s[b] = p + w[kOffB3];
+}
+
+hipError_t launch_mlp_fwd(const float *w, const float *mean, const float *std, const float *X, int64_t B,
+                          float *logits, hipStream_t s) {
+  hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, w, mean, std, X, B, logits);
+  return hipGetLastError();
 }
 
 // tanh form of GELU and its derivative, (1 + tanh u) / 2 as 1 / (1 + exp(-2u)).
@@ -490,7 +481,6 @@ struct sph_mlp {
   int64_t max_batch;
   hipStream_t s;
   float *w, *g, *m, *v, *mean, *std;
-  float *xs, *z1, *z2, *a2;  // activations the forward pass stores
   float *part;               // the gradient kernel's block sums
   float *loss, *loss_acc;
   int64_t step;
@@ -523,10 +513,6 @@ size_t mlp_carve(sph_mlp *m, uintptr_t base, int64_t B) {
   m->v = take(kMlpParams);
   m->mean = take(kMlpIn);
   m->std = take(kMlpIn);
-  m->xs = take(B * kMlpIn);
-  m->z1 = take(B * kMlpHid);
-  m->z2 = take(B * kMlpHid);
-  m->a2 = take(B * kMlpHid);
   m->part = take(std::min<int64_t>(kGradBlocks, (B + kGradWaves - 1) / kGradWaves) * kPart);  // any batch up to B
   m->loss = take(1);
   m->loss_acc = take(1);
@@ -553,36 +539,6 @@ AdamArgs adam_next(sph_mlp *m, float lr, float b1, float b2, float eps) {
   const float c1 = 1.0f - std::pow(b1, (float)m->step);
   const float c2 = 1.0f - std::pow(b2, (float)m->step);
   return AdamArgs{m->w, m->m, m->v, lr, b1, b2, eps, c1, c2};
-}
-
-}  // namespace
-
-// Scratch of sph_mlp_forward_noalloc: the activations k_mlp_fwd stores
-// (standardised input, both pre-activations, the second activation) for up
-// to SPH_MLP_NOALLOC_MAX_ROWS rows, in a fixed device array (each device
-// that runs the library holds its own copy).  Host code never passes the
-// array's name to a kernel: its device address is looked up once per device
-// (hipGetSymbolAddress, with that device current) and kept.
-static __device__ __align__(256) float scratch[(size_t)SPH_MLP_NOALLOC_MAX_ROWS * (kMlpIn + 3 * kMlpHid)];
-
-namespace {
-
-constexpr int kScratchDevices = 64;
-std::mutex g_scratch_mu;
-float *g_scratch_ptr[kScratchDevices] = {};
-
-// Device address of the current device's scratch array.
-sph_status noalloc_scratch(float **out) {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScratchDevices) return SPH_EHIP;
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (g_scratch_ptr[dev] == nullptr) {
-    void *p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || p == nullptr) return SPH_EHIP;
-    g_scratch_ptr[dev] = static_cast<float *>(p);
-  }
-  *out = g_scratch_ptr[dev];
-  return SPH_OK;
 }
 
 }  // namespace
@@ -628,10 +584,7 @@ void sph_mlp_destroy(sph_mlp *m) { delete m; }
 sph_status sph_mlp_forward(sph_mlp *m, const float *X, int64_t B, float *logits) {
   if (!m || !X || !logits || B < 0 || B > m->max_batch) return SPH_EINVAL;
   if (B == 0) return SPH_OK;
-  const unsigned rb = (unsigned)((B + 3) / 4);
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(rb), dim3(256), 0, m->s, m->w, m->mean, m->std, X, (const int32_t *)nullptr,
-                     (int64_t)0, B, m->xs, m->z1, m->z2, m->a2, logits);
-  return hipGetLastError() == hipSuccess ? SPH_OK : SPH_EHIP;
+  return launch_mlp_fwd(m->w, m->mean, m->std, X, B, logits, m->s) == hipSuccess ? SPH_OK : SPH_EHIP;
 }
 
 sph_status sph_mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const float *w, int64_t B, float *loss,
@@ -684,16 +637,7 @@ sph_status sph_mlp_forward_noalloc(const float *params, const float *mean, const
                                    int64_t B, float *logits, void *hip_stream) {
   if (!params || !mean || !std || !X || !logits || B < 0 || B > SPH_MLP_NOALLOC_MAX_ROWS) return SPH_EINVAL;
   if (B == 0) return SPH_OK;
-  float *sp = nullptr;
-  if (noalloc_scratch(&sp) != SPH_OK) return SPH_EHIP;
-  float *xs = sp;
-  float *z1 = xs + (size_t)SPH_MLP_NOALLOC_MAX_ROWS * kMlpIn;
-  float *z2 = z1 + (size_t)SPH_MLP_NOALLOC_MAX_ROWS * kMlpHid;
-  float *a2 = z2 + (size_t)SPH_MLP_NOALLOC_MAX_ROWS * kMlpHid;
-  const unsigned rb = (unsigned)((B + 3) / 4);
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(rb), dim3(256), 0, (hipStream_t)hip_stream, params, mean, std, X,
-                     (const int32_t *)nullptr, (int64_t)0, B, xs, z1, z2, a2, logits);
-  return hipGetLastError() == hipSuccess ? SPH_OK : SPH_EHIP;
+  return launch_mlp_fwd(params, mean, std, X, B, logits, (hipStream_t)hip_stream) == hipSuccess ? SPH_OK : SPH_EHIP;
 }
 
 sph_status sph_mlp_infer_bf16(const float *params, const float *mean, const float *std, const float *X, int64_t n,
