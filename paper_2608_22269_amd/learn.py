@@ -73,7 +73,9 @@ class MLPTrainer:
         if nbytes == 0:
             raise L.SphError(L.SPH_EINVAL, "sph_mlp_workspace_bytes")
         self._ws, ptr = device_buffer(nbytes)
-        self.stream = stream if stream is not None else torch.cuda.current_stream()
+        cur = torch.cuda.current_stream()
+        self.stream = stream if stream is not None else cur
+        self._side = self.stream != cur
         _lend(self.stream, self._ws)
         p0 = np.ascontiguousarray(params0, dtype=np.float32)
         mu = np.ascontiguousarray(mean, dtype=np.float32)
@@ -127,7 +129,8 @@ class MLPTrainer:
     def train_epoch(self, Xd, yd, wd, perm_d, batch, lr):
         """One epoch over device tensors (X n x 16 f32, y, w f32, perm int32)."""
         ml = C.c_float(0.0)
-        _lend(self.stream, Xd, yd, wd, perm_d)
+        if self._side:  # asking for the current stream takes 3 us of some 320
+            _lend(self.stream, Xd, yd, wd, perm_d)
         _check(L.lib().sph_mlp_train_epoch(self.h, C.c_void_p(Xd.data_ptr()), C.c_void_p(yd.data_ptr()),
                                            C.c_void_p(wd.data_ptr()) if wd is not None else None,
                                            C.c_void_p(perm_d.data_ptr()), Xd.shape[0], int(batch), float(lr),
