@@ -612,7 +612,6 @@ inline unsigned candidate_grid(int64_t nf) {
 struct Ctx;  // host context (api.hip)
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s);
 // exclusive scan of n u32 values into out (out may alias in); total written
 // to out[n]; tmp needs scan_tmp_words(n) words.
 constexpr int kScanTile = 1024;

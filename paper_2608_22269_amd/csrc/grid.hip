@@ -25,20 +25,9 @@ __global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t n) {
   if (i < n) p[i] = v;
 }
 
-__global__ void k_fill_u64(unsigned long long *p, unsigned long long v, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n)), dim3(kBlock), 0, s, p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(n)), dim3(kBlock), 0, s, p, v, n);
   return hipGetLastError();
 }
 
