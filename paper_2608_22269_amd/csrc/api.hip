@@ -449,13 +449,16 @@ sph_status rebuild(sph_ctx *c, int with_stage0) {
   if (!c->mixed) {
     e = launch_sort_keys(c->g, c->dim, c->cur.x[0], c->cur.x[1], c->cur.x[2], nullptr, c->nf, c->cur.id, c->ss,
                          c->cs_f, c->perm, c->sc, c->s, &c->P, &q);
-    if (e == hipSuccess) e = launch_reorder_f64(c->P, c->ss, c->cs_f, c->perm, c->nf, c->cur, c->alt, c->rec0, c->rec1, with_stage0, c->s);
+    if (e == hipSuccess)
+      e = launch_reorder_f64(c->P, c->ss, c->cs_f, c->perm, c->nf, c->cur, c->alt, c->rec0, c->rec1, with_stage0,
+                             c->s);
     std::swap(c->cur, c->alt);
   } else {
     e = launch_sort_keys(c->g, c->dim, nullptr, nullptr, nullptr, c->mcur.cell, c->nf, c->mcur.id, c->ss, c->cs_f,
                          c->perm, c->sc, c->s, &c->P, &q);
     if (e == hipSuccess)
-      e = launch_reorder_mixed(c->P, c->g, c->ss, c->cs_f, c->perm, c->nf, c->mcur, c->malt, c->mrec, with_stage0, c->s);
+      e = launch_reorder_mixed(c->P, c->g, c->ss, c->cs_f, c->perm, c->nf, c->mcur, c->malt, c->mrec, with_stage0,
+                               c->s);
     std::swap(c->mcur, c->malt);
   }
   c->cells_current = true;
@@ -493,10 +496,10 @@ sph_status move_body(sph_ctx *c) {
   return hip_check(c, e, "body motion");
 }
 
-// One right-hand side (its bookkeeping in c->prep, unless the sort ran it).  mode: the pair pass's kPairSearch / kPairSearchKeep /
-// kPairKept; win_extra widens the cell searches of the mirror and scan passes
-// (over the cells of the kept lists' build: the bound on any particle's move
-// since).
+// One right-hand side (its bookkeeping in c->prep, unless the sort ran it).
+// mode: the pair pass's kPairSearch / kPairSearchKeep / kPairKept; win_extra
+// widens the cell searches of the mirror and scan passes (over the cells of
+// the kept lists' build: the bound on any particle's move since).
 sph_status rhs(sph_ctx *c, int mode = kPairSearch, double win_extra = 0.0) {
   hipError_t e = hipSuccess;
   if (c->prep.on) e = launch_prep(c->P, take_prep(c), c->sc, c->s);  // no sort ran it
@@ -1279,7 +1282,8 @@ extern "C" sph_status sph_fields(sph_ctx *c, int32_t field, void *out, int32_t o
     if (e == hipSuccess && (field == SPH_FIELD_X || field == SPH_FIELD_MASS))
       e = launch_export_rows(zero, fid, 0, field == SPH_FIELD_X ? soa(c->dm.x, dim) : one(c->dm.m), did, nd,
                              field == SPH_FIELD_X ? dim : 1, dd, s, nout);
-    if (e == hipSuccess && (field == SPH_FIELD_U || field == SPH_FIELD_PHI || field == SPH_FIELD_RHO || field == SPH_FIELD_P))
+    if (e == hipSuccess &&
+        (field == SPH_FIELD_U || field == SPH_FIELD_PHI || field == SPH_FIELD_RHO || field == SPH_FIELD_P))
       e = launch_dummy_fields_mixed(c->P, c->mrec, nf, did, nd, field, dst, s, nout);
   } else {
     switch (field) {
@@ -1289,7 +1293,8 @@ extern "C" sph_status sph_fields(sph_ctx *c, int32_t field, void *out, int32_t o
       case SPH_FIELD_MASS: e = rows(one(c->cur.m), one(c->dm.m), 1); break;
       case SPH_FIELD_RHO: case SPH_FIELD_P:
         e = launch_rho_p(c->P, c->cur.phi, fid, nf, dd, field == SPH_FIELD_RHO ? 0 : 1, s, nout);
-        if (e == hipSuccess) e = launch_rho_p_rec(c->P, c->rec0 + nf, did, nd, dd, field == SPH_FIELD_RHO ? 0 : 1, s, nout);
+        if (e == hipSuccess)
+          e = launch_rho_p_rec(c->P, c->rec0 + nf, did, nd, dd, field == SPH_FIELD_RHO ? 0 : 1, s, nout);
         break;
       case SPH_FIELD_CELL: {
         const double *xx[3] = {c->cur.x[0], c->cur.x[1], c->cur.x[2]};
@@ -1309,12 +1314,14 @@ extern "C" sph_status sph_fields(sph_ctx *c, int32_t field, void *out, int32_t o
       case SPH_FIELD_LOGIT: e = words(c->r.logit, 0xffffffffu, 0, 1); break;
       case SPH_FIELD_FS_PATH:
         if (c->n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->n)), dim3(kBlock), 0, s, di, 0, c->n);
-        if (nf > 0) hipLaunchKernelGGL(k_path_of, dim3(grid_for(nf)), dim3(kBlock), 0, s, c->r.flags, fid, nf, di, nout);
+        if (nf > 0)
+          hipLaunchKernelGGL(k_path_of, dim3(grid_for(nf)), dim3(kBlock), 0, s, c->r.flags, fid, nf, di, nout);
         break;
       case SPH_FIELD_MIRROR_SRC:
         if (c->n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->n)), dim3(kBlock), 0, s, di, -1, c->n);
         if (nd > 0)
-          hipLaunchKernelGGL(k_mirror_src_ids, dim3(grid_for(nd)), dim3(kBlock), 0, s, c->dm.src, did, fid, nd, di, nout);
+          hipLaunchKernelGGL(k_mirror_src_ids, dim3(grid_for(nd)), dim3(kBlock), 0, s, c->dm.src, did, fid, nd, di,
+                             nout);
         break;
       default: break;
     }

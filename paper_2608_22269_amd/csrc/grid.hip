@@ -413,14 +413,15 @@ __global__ void __launch_bounds__(256) k_reorder_f64(Phys P, SortScratch ss, con
 }
 
 hipError_t launch_reorder_f64(const Phys &P, const SortScratch &ss, const uint32_t *start, const uint2 *perm,
-                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s) {
+                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1,
+                              int with_stage0, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (P.dim == 2)
-    hipLaunchKernelGGL(k_reorder_f64<2>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0, rec1,
-                       with_stage0);
+    hipLaunchKernelGGL(k_reorder_f64<2>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0,
+                       rec1, with_stage0);
   else
-    hipLaunchKernelGGL(k_reorder_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0, rec1,
-                       with_stage0);
+    hipLaunchKernelGGL(k_reorder_f64<3>, dim3(grid_for(n)), dim3(kBlock), 0, s, P, ss, start, perm, n, src, dst, rec0,
+                       rec1, with_stage0);
   return hipGetLastError();
 }
 

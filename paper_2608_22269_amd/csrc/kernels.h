@@ -32,7 +32,8 @@ hipError_t launch_sort_keys(const Grid &g, int dim, const double *x, const doubl
 int64_t fused_scan_tiles(int64_t nkey);
 hipError_t launch_prep(const Phys &P, const StepPrep &prep, Scalars *sc, hipStream_t s);
 hipError_t launch_reorder_f64(const Phys &P, const SortScratch &ss, const uint32_t *start, const uint2 *perm,
-                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1, int with_stage0, hipStream_t s);
+                              int64_t n, const FluidF64 &src, const FluidF64 &dst, double4 *rec0, double4 *rec1,
+                              int with_stage0, hipStream_t s);
 // records of the FP64 state in its current order (no sort)
 hipError_t launch_refresh_f64(const Phys &P, const FluidF64 &f, int64_t n, double4 *rec0, double4 *rec1,
                               hipStream_t s);

@@ -19,8 +19,8 @@ struct MixedRec {
 hipError_t launch_to_mixed(const Phys &P, const Grid &g, const FluidF64 &src, int64_t nf, const FluidMixed &dst,
                            Scalars *sc, hipStream_t s);
 hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const SortScratch &ss, const uint32_t *start,
-                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst, const MixedRec &rec, int with_stage0,
-                                hipStream_t s);
+                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst,
+                                const MixedRec &rec, int with_stage0, hipStream_t s);
 hipError_t launch_mirror_mixed(const Phys &P, const Grid &g, const Dummies &d, int64_t nd, const MixedRec &rec,
                                const uint32_t *cs_f, uint32_t nf, const Scalars *sc, hipStream_t s,
                                const uint32_t *fid);

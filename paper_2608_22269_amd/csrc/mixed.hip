@@ -163,7 +163,8 @@ __global__ void __launch_bounds__(256) k_reorder_mixed(Phys P, Grid g, SortScrat
 }
 
 hipError_t launch_reorder_mixed(const Phys &P, const Grid &g, const SortScratch &ss, const uint32_t *start,
-                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst, const MixedRec &rec, int with_stage0, hipStream_t s) {
+                                const uint2 *perm, int64_t nf, const FluidMixed &src, const FluidMixed &dst,
+                                const MixedRec &rec, int with_stage0, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
   if (P.dim == 2)
     hipLaunchKernelGGL(k_reorder_mixed<2>, dim3(grid_for(nf)), dim3(kBlock), 0, s, P, g, ss, start, perm, nf, src, dst,
@@ -300,8 +301,9 @@ hipError_t launch_mirror_mixed(const Phys &P, const Grid &g, const Dummies &d, i
                                const uint32_t *fid) {
   if (nd <= 0) return hipSuccess;
   const bool team = nd <= kMirrorTeamRowsMixed;
-#define WB_GO(D, T) \
-  hipLaunchKernelGGL((k_mirror_mixed<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec, cs_f, nf, sc, fid)
+#define WB_GO(D, T)                                                                                                  \
+  hipLaunchKernelGGL((k_mirror_mixed<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec,   \
+                     cs_f, nf, sc, fid)
   if (P.dim == 2 && team) WB_GO(2, kMirrorTeam);
   else if (P.dim == 2) WB_GO(2, 1);
   else if (team) WB_GO(3, kMirrorTeam);
@@ -732,7 +734,8 @@ __global__ void __launch_bounds__(kSearchBlock) WB_MIXED_ATTR
   coop_init(cw, g, active, (float)rho, DIM);
   for (;;) {
     const bool fin =
-        coop_fill<DIM, kMList, kMBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kSearchBlock, cnt, S.ntest, load, near);
+        coop_fill<DIM, kMList, kMBatch>(cw, g, cs_f, cs_d, nf, cp, &list[0][tid], kSearchBlock, cnt, S.ntest, load,
+                                        near);
     run_list(cnt);
     cnt = 0;
     if (fin) break;

@@ -125,11 +125,10 @@ __device__ __forceinline__ float dot(float c, const float *a, const float *b) {
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
-__global__ void __launch_bounds__(64 * kGradWaves, 2) k_mlp_grad(const float *__restrict__ w, const float *__restrict__ mean,
-                                                     const float *__restrict__ std, const float *__restrict__ X,
-                                                     const float *__restrict__ y, const float *__restrict__ wt,
-                                                     const int32_t *__restrict__ perm, int64_t off, int64_t B, int rpw,
-                                                     float *__restrict__ part) {
+__global__ void __launch_bounds__(64 * kGradWaves, 2)
+    k_mlp_grad(const float *__restrict__ w, const float *__restrict__ mean, const float *__restrict__ std,
+               const float *__restrict__ X, const float *__restrict__ y, const float *__restrict__ wt,
+               const int32_t *__restrict__ perm, int64_t off, int64_t B, int rpw, float *__restrict__ part) {
   __shared__ __align__(16) float sx[kGradWaves][kMlpIn], sa[kGradWaves][kMlpHid], sd[kGradWaves][kMlpHid];
   __shared__ __align__(16) float w2l[kMlpHid][kMlpHid + 4];  // rows of W2 (a stride of 68: 16 lanes on all banks)
   __shared__ float sum[kGradWaves / 2][kPart];
@@ -304,11 +303,10 @@ __device__ __forceinline__ __bf16 to_bf16(float x) { return (__bf16)x; }
 // next tile's features requested a tile ahead, at three waves per SIMD (two:
 // 1.05 ms); the GELUs' instructions alone (96 of 160 cycles of exp2 and
 // reciprocal at a quarter rate among them) take about 0.85 ms.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_mlp_infer_bf16(const float *__restrict__ w, const float *__restrict__ mean,
-                                                        const float *__restrict__ std, const float *__restrict__ X,
-                                                        const uint32_t *__restrict__ rows,
-                                                        const uint32_t *__restrict__ nrows_dev, int64_t n,
-                                                        float *__restrict__ logits) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+    k_mlp_infer_bf16(const float *__restrict__ w, const float *__restrict__ mean, const float *__restrict__ std,
+                     const float *__restrict__ X, const uint32_t *__restrict__ rows,
+                     const uint32_t *__restrict__ nrows_dev, int64_t n, float *__restrict__ logits) {
   // biases and output weights per wave (in 48 registers they spill at three
   // waves per SIMD)
   __shared__ __align__(16) float vec[4][3][kMlpHid];
@@ -526,8 +524,8 @@ hipError_t mlp_loss_grad(sph_mlp *m, const float *X, const float *y, const float
                          int64_t B, float *acc, int acc_reset, const AdamArgs *adam) {
   int rpw, nblk;
   grad_split(B, rpw, nblk);
-  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(64 * kGradWaves), 0, m->s, m->w, m->mean, m->std, X, y, w, perm, off,
-                     B, rpw, m->part);
+  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nblk), dim3(64 * kGradWaves), 0, m->s, m->w, m->mean, m->std, X, y, w,
+                     perm, off, B, rpw, m->part);
   hipLaunchKernelGGL(k_mlp_reduce, dim3((kPart + kRedParams - 1) / kRedParams), dim3(kRedParams * kRedSlices), 0, m->s,
                      m->part, nblk, B, m->g, m->loss, acc, acc_reset, adam ? 1 : 0, adam ? *adam : AdamArgs{});
   return hipGetLastError();

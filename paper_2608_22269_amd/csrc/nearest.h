@@ -173,8 +173,8 @@ __device__ __forceinline__ int64_t nearest_fluid(RowWalker &w, const Grid &g, co
     for (int t = -d; t < d; t += DIM == 3 ? 2 : 2 * d) {
       if (DIM == 3) {
         const int side = sub / 2, at = t + sub % 2;
-        window(side == 0 ? at : side == 1 ? d : side == 2 ? -at : -d, side == 0 ? -d : side == 1 ? at : side == 2 ? d : -at,
-               true, lo, hi);
+        window(side == 0 ? at : side == 1 ? d : side == 2 ? -at : -d,
+               side == 0 ? -d : side == 1 ? at : side == 2 ? d : -at, true, lo, hi);
       } else {
         window(sub == 0 ? -d : d, 0, sub < 2, lo, hi);
       }

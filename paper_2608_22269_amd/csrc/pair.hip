@@ -191,10 +191,10 @@ __device__ __forceinline__ void pair_body_f64(const Phys &P, const double4 &a0, 
 // for the later right-hand sides; a lane with more than kKeepChunks fills
 // raises sc->vovf.
 template <int DIM, bool PST4, bool KEEP>
-__global__ void __launch_bounds__(kSearchBlock) WB_PAIR_ATTR k_pair_f64(Phys P, Grid g, const double4 *__restrict__ rec0,
-                                                  const double4 *__restrict__ rec1, const uint32_t *__restrict__ cs_f,
-                                                  const uint32_t *__restrict__ cs_d, uint32_t nf, Scalars *sc,
-                                                  Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
+__global__ void __launch_bounds__(kSearchBlock) WB_PAIR_ATTR
+    k_pair_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 *__restrict__ rec1,
+               const uint32_t *__restrict__ cs_f, const uint32_t *__restrict__ cs_d, uint32_t nf, Scalars *sc,
+               Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
   __shared__ uint32_t list[kList][kSearchBlock];
   const int tid = threadIdx.x;
   const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kSearchBlock + tid;
@@ -292,10 +292,9 @@ __global__ void __launch_bounds__(kSearchBlock) WB_PAIR_ATTR k_pair_f64(Phys P, 
 // fits the skin: a pair within 2h now was within 2h + skin then, so the
 // neighbour sets are those of a fresh search.
 template <int DIM, bool PST4>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WB_KEPT_WAVES))) k_pair_kept_f64(Phys P, const double4 *__restrict__ rec0,
-                                                                    const double4 *__restrict__ rec1, uint32_t nf,
-                                                                    Scalars *sc, Rates out,
-                                                                    uint32_t *__restrict__ cand, KeptLists kl) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WB_KEPT_WAVES)))
+    k_pair_kept_f64(Phys P, const double4 *__restrict__ rec0, const double4 *__restrict__ rec1, uint32_t nf,
+                    Scalars *sc, Rates out, uint32_t *__restrict__ cand, KeptLists kl) {
   __shared__ uint32_t list[kList][kBlock];
   const int tid = threadIdx.x;
   const uint32_t i = xcd_block(blockIdx.x, gridDim.x) * kBlock + tid;
@@ -702,7 +701,8 @@ void launch_pair_f64_inst(const Phys &P, const Grid &g, const double4 *rec0, con
 
 hipError_t launch_pair_f64(const Phys &P, const Grid &g, const double4 *rec0, const double4 *rec1,
                            const uint32_t *cs_f, const uint32_t *cs_d, uint32_t nf, int64_t nrec, Scalars *sc,
-                           const Rates &out, uint32_t *cand, int mode, uint32_t *kent, unsigned long long *kcnt, hipStream_t s) {
+                           const Rates &out, uint32_t *cand, int mode, uint32_t *kent, unsigned long long *kcnt,
+                           hipStream_t s) {
   if (nf == 0) return hipSuccess;
   if (mode != kPairSearch && (!kent || !kcnt)) return hipErrorInvalidValue;
   KeptLists kl{kent, kcnt};
@@ -964,8 +964,9 @@ hipError_t launch_mirror_f64(const Phys &P, const Grid &g, const Dummies &d, int
                              uint32_t nf, const Scalars *sc, hipStream_t s, const uint32_t *fid) {
   if (nd == 0) return hipSuccess;
   const bool team = nd <= kMirrorTeamRows;
-#define WB_GO(D, T) \
-  hipLaunchKernelGGL((k_mirror_f64<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec0, rec1, drec0, drec1, cs_f, nf, sc, fid)
+#define WB_GO(D, T)                                                                                                \
+  hipLaunchKernelGGL((k_mirror_f64<D, T>), dim3(grid_for(nd, kBlock / T)), dim3(kBlock), 0, s, P, g, d, nd, rec0,   \
+                     rec1, drec0, drec1, cs_f, nf, sc, fid)
   if (P.dim == 2 && team) WB_GO(2, kMirrorTeam);
   else if (P.dim == 2) WB_GO(2, 1);
   else if (team) WB_GO(3, kMirrorTeam);
