@@ -299,10 +299,13 @@ __device__ __forceinline__ __bf16 to_bf16(float x) { return (__bf16)x; }
 // loaded in that order -- slot (grp, e) of K block q is unit 16 (2 q + e / 4)
 // + 4 grp + e % 4.  So the activations stay in registers (rows x units needed
 // an exchange through LDS and 16 cross-lane sums per tile where this needs
-// 2).  17,500,000 rows: 1.41 ms before, 1.28 ms transposed, 0.91 ms with the
+// 2).  17,500,000 rows, whole calls one after another, the weights uploaded by
+// three transfers each: 1.41 ms before, 1.28 ms transposed, 0.91 ms with the
 // next tile's features requested a tile ahead, at three waves per SIMD (two:
-// 1.05 ms); the GELUs' instructions alone (96 of 160 cycles of exp2 and
-// reciprocal at a quarter rate among them) take about 0.85 ms.
+// 1.05 ms); with one transfer 0.88 ms, and the kernel alone 0.99 ms under
+// rocprofv3, at its lower clock.  The GELUs' instructions alone (96 of 160
+// cycles of exp2 and reciprocal at a quarter rate among them) take about
+// 0.85 ms.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
     k_mlp_infer_bf16(const float *__restrict__ w, const float *__restrict__ mean, const float *__restrict__ std,
                      const float *__restrict__ X, const uint32_t *__restrict__ rows,

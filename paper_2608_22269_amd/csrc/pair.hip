@@ -432,15 +432,22 @@ __device__ __forceinline__ const double4 &rec_at(const double4 *rec, uint32_t j)
 // several times eight records and is tested in place; else the windows' record
 // indices are first listed in LDS, so that the short rows fill the lanes (the
 // other way round 928 against 637 us at 651,000 particles, cells of 2h, and 710
-// against 565, cells of h; in 2D both take the same).  Neighbour number n goes to lane n mod 8 wherever the list is
-// emptied, so this kernel's plain search, the one that keeps its candidates
-// (kPairSearchKeep: radius 2h + skin) and its pass from kept candidates
-// (kPairKept, lists built by this kernel only: full chunks but the last) give
-// the same sums bit for bit.
+// against 565, cells of h; in 2D both take the same).  Neighbour number n goes
+// to lane n mod 8 wherever the list is emptied, so this kernel's plain search,
+// the one that keeps its candidates (kPairSearchKeep: radius 2h + skin) and its
+// pass from kept candidates (kPairKept, lists built by this kernel only: full
+// chunks but the last) give the same sums bit for bit.  The two searches
+// always come from the same kernel (by_team); above 70,000 particles in 3D
+// (35,000 in 2D) its lists are read by k_pair_kept_f64, whose sums are rounded
+// otherwise.
 // Everything that crosses lanes sits under scalar control flow: trip counts
-// come from ballots and lane reads, and list stores are unconditional (a lane
-// without an entry stores to a spare slot).  A conditional store before a loop
-// that ballots let the compiler run the loop with part of the wave.
+// come from ballots and lane reads, and stores to the team's list are
+// unconditional (a lane without an entry stores to a spare slot).  A
+// conditional store right before a loop that ballots let the compiler merge
+// the store's branch with the loop's and run it with part of the wave.  So
+// where lanes do something of their own (a kept entry, a row's window, a
+// neighbour's body) a wave barrier follows: it can't be made conditional, and
+// all lanes are back before the next ballot.
 template <int DIM, bool PST4, int MODE, bool LONG>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PST4 ? 4 : 2)))
 k_pair_team_f64(Phys P, Grid g, const double4 *__restrict__ rec0, const double4 *__restrict__ rec1,
